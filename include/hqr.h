@@ -72,7 +72,8 @@ extern "C" {
 /* Precision of the trailing-update contractions. */
 #define HQR_PREC_FP64  0 /* everything FP64                                  */
 #define HQR_PREC_MIXED 1 /* trailing update on FP32 MFMA with FP32
-                            accumulation, subtracted into FP64 storage;
+                            accumulation, subtracted into FP64 storage (with
+                            look-ahead the next panel's 64 columns take FP64);
                             reflector generation, R's diagonal, Q^T b and
                             the back-substitution stay FP64, then
                             refinement of the semi-normal equations with
