@@ -32,15 +32,15 @@
 // The decision is taken on the device: `flag` then makes pass 2 run the exact
 // loop instead.
 //
-// A panel takes two kernels, each a grid-wide step whose reduction and
-// small-matrix stage run in the workgroup that finishes last:
-//   cqr_pass1_kernel  (previous panel's update of these columns +) Gram
-//                     partials -> G -> R1, R1^{-1}
-//   cqr_pass2_kernel  Q1 and its Gram partials -> G2 -> R2 -> reconstruction
-// and the bottom rows become V_bot = A_bot W^{-1} in narrow_vtx_kernel (which
+// Each pass is a kernel that forms Gram partials (cqr_gram1_kernel, which also
+// applies the previous panel's update to these columns; cqr_gram2_kernel), one
+// that sums them (gram_reduce_kernel) and one workgroup for the small matrices
+// (cqr_chol_kernel), and the bottom rows become V_bot = A_bot W^{-1} in narrow_vtx_kernel (which
 // also forms W = T^T V^T C for the next panel's columns, with look-ahead) or
 // cqr_finish_kernel.
 #pragma once
+
+#include <utility>
 
 #include "hqr_args.hpp"
 
@@ -181,20 +181,202 @@ HQR_DEV double recip_nr(double u)
     return fma(y, e, y);
 }
 
+// r = 1/sqrt(d) on a pivot chain: the hardware reciprocal square root (about
+// 2^-24 relative) and one cubic step, r = y (1 + e/2 + 3 e^2/8) with
+// e = 1 - d y^2, exact to below FP64 rounding in four dependent operations
+// (two coupled Newton steps take seven).  d <= 0 (or NaN) gives a value that
+// is not finite or not meaningful; the caller flags such pivots.
+HQR_DEV double pivot_rsqrt(double d)
+{
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = fma(-(d * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// pivot_rsqrt cut into its dependent stages, so that independent updates can
+// be placed between them (y holds the result after stage 3).
+struct PivotChain {
+    double d, y, t, e, a, b;
+    __device__ __forceinline__ void start(double dv)
+    {
+        d = dv;
+        y = __builtin_amdgcn_rsq(d);
+        pin(y);
+    }
+    template <int U> __device__ __forceinline__ void stage()
+    {
+        if constexpr (U == 0) {
+            t = d * y;
+            pin(t);
+        } else if constexpr (U == 1) {
+            e = fma(-t, y, 1.0);
+            pin(e);
+        } else if constexpr (U == 2) {
+            a = y * e;
+            b = fma(e, 0.375, 0.5);
+            pin(a);
+            pin(b);
+        } else if constexpr (U == 3) {
+            y = fma(a, b, y);
+            pin(y);
+        }
+    }
+};
+
+// recip_nr in stages, the same way.
+struct RecipChain {
+    double u0, y, e;
+    __device__ __forceinline__ void start(double u)
+    {
+        u0 = u;
+        y = __builtin_amdgcn_rcp(u);
+        pin(y);
+    }
+    template <int U> __device__ __forceinline__ void stage()
+    {
+        if constexpr (U == 0 || U == 2) {
+            e = fma(-u0, y, 1.0);
+            pin(e);
+        } else if constexpr (U == 1 || U == 3) {
+            y = fma(y, e, y);
+            pin(y);
+        }
+    }
+};
+
+// The transposed block product Y^T = sum_k MB[16k.., 16j..]^T MA[16i.., 16k..]^T
+// (k = k0 .. k1-1) in D layout, i.e. D[a][b] = Y[b][a] with
+// Y = sum_k MA_ik MB_kj.
+HQR_DEV f64x4 mma_sum_t(const double (*MA)[LD65], int i, const double (*MB)[LD65], int j, int k0, int k1, int lane)
+{
+    const int i16 = lane & 15, kk = lane >> 4;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int k = k0; k < k1; ++k) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = 16 * k + 4 * q + kk;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(MB[r][16 * j + i16], MA[16 * i + i16][r], acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
+// X_ij = -Y X_jj for an upper inverse whose diagonal block X_jj is in place,
+// from Y^T in D layout (mma_sum_t): X_ij^T = -X_jj^T Y^T.
+HQR_DEV void inv_upper_close(double (*X)[LD65], int i, int j, f64x4 yt, int lane)
+{
+    const int i16 = lane & 15, kk = lane >> 4;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[16 * j + 4 * q + kk][16 * j + i16], yt[q], acc, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) X[16 * i + i16][16 * j + 4 * q + kk] = -acc[q];
+}
+
+// Trailing block update M_ij -= MA_i^T-or-L rows of block step b0 on MFMA:
+// the Cholesky form M_ij -= G_bi^T G_bj over the rows b0 .. b0 + 15.
+HQR_DEV void chol_trail_blk(double (*G)[LD65], int b0, int ib, int jb, int lane)
+{
+    const int i16 = lane & 15, kk = lane >> 4;
+    f64x4 acc = ld_blk(G, 16 * ib, 16 * jb, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int k = b0 + 4 * q + kk;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-G[k][16 * ib + i16], G[k][16 * jb + i16], acc, 0, 0, 0);
+    }
+    st_blk(G, 16 * ib, 16 * jb, acc, 1.0, lane);
+}
+
+// One pivot of the 16 x 16 elimination in chol64_dpp: on entry d is pivot I
+// and r its reciprocal root, on exit those of pivot I + 1.  Row I + 1 is
+// updated first; its pivot's reciprocal root is then formed, a stage at a
+// time, between the updates of the other rows (two rows' broadcasts together,
+// so no FMA waits for its broadcast).  Templates rather than unrolled loops:
+// every register index has to be static.
+template <int I, int U>
+HQR_DEV void chol16_rows(double (&g)[16], double (&z)[16], double vg, double vz, PivotChain &pc)
+{
+    constexpr int i2 = I + 2 + 2 * U;
+    if constexpr (i2 < 16) {
+        double ta = bc16c<i2>(vg), tb;
+        pin(ta);
+        if constexpr (i2 + 1 < 16) {
+            tb = bc16c<i2 + 1>(vg);
+            pin(tb);
+        }
+        g[i2] = fma(-ta, vg, g[i2]);
+        z[i2] = fma(-ta, vz, z[i2]);
+        pin(g[i2]);
+        pin(z[i2]);
+        if constexpr (i2 + 1 < 16) {
+            g[i2 + 1] = fma(-tb, vg, g[i2 + 1]);
+            z[i2 + 1] = fma(-tb, vz, z[i2 + 1]);
+            pin(g[i2 + 1]);
+            pin(z[i2 + 1]);
+        }
+    }
+    pc.template stage<U>();
+}
+
+template <int I>
+HQR_DEV void chol16_pivot(double (&g)[16], double (&z)[16], double &d, double &r, double &my_d, int jj)
+{
+    const double vg = g[I] * r, vz = z[I] * r;
+    g[I] = vg;
+    z[I] = vz;
+    my_d = (jj == I) ? d : my_d;
+    if constexpr (I < 15) {
+        const double t1 = bc16c<I + 1>(vg);
+        g[I + 1] = fma(-t1, vg, g[I + 1]);
+        pin(g[I + 1]);
+        d = bc16c<I + 1>(g[I + 1]);
+        pin(d);
+        z[I + 1] = fma(-t1, vz, z[I + 1]);
+        PivotChain pc;
+        pc.start(d);
+        chol16_rows<I, 0>(g, z, vg, vz, pc);
+        chol16_rows<I, 1>(g, z, vg, vz, pc);
+        chol16_rows<I, 2>(g, z, vg, vz, pc);
+        chol16_rows<I, 3>(g, z, vg, vz, pc);
+        chol16_rows<I, 4>(g, z, vg, vz, pc);
+        chol16_rows<I, 5>(g, z, vg, vz, pc);
+        chol16_rows<I, 6>(g, z, vg, vz, pc);
+        r = pc.y;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int... Is>
+HQR_DEV void chol16_pivots(double (&g)[16], double (&z)[16], double &d, double &r, double &my_d, int jj,
+                           std::integer_sequence<int, Is...>)
+{
+    (chol16_pivot<Is>(g, z, d, r, my_d, jj), ...);
+}
+
 // In-place upper Cholesky G = R^T R of the n x n leading block of G (R in the
 // upper triangle, zeros below, identity beyond n; G's entries outside the
-// block must be zero), right-looking by 16-column block steps.
+// block must be zero) and X = R^{-1} (zeros below), right-looking by
+// 16-column block steps; 256 threads.
 //
-// Block step kb: wave 0 factors block row kb in registers.  Lane t holds
-// column 16kb + t of the block row, and every 16-lane row also holds a copy
-// of the diagonal block (lane 16r + j: its column j), so the entries of the
-// current row of R that a rank-1 update needs are taken from the lane's own
-// row by DPP broadcast.  The same wave then inverts the diagonal block by back
-// substitution into X's diagonal block.  All waves then subtract
-// R_kb^T R_kb from the trailing upper blocks on MFMA.
+// Bound: the serial chain of 64 pivots in one wave.  Block step kb: wave 0
+// eliminates [G_kk | I | G_k,kb+1.. ] in registers: every 16-lane row holds a
+// copy of the diagonal block (lane 16r + j: its column j, array g), and array
+// z holds an identity column in the lanes of row 0 and the columns of the
+// block row in rows 1..3, so one broadcast and two FMAs per entry of R give
+// R_kk, R_kk^{-T} and the block row; R_kk^{-T}'s column j is row j of
+// X_kk.  No lane masks inside: entries of g left of the pivot are never read.
+// Waves 1..3 meanwhile do what the next pivots do not need: the trailing
+// blocks outside block row kb (of the previous step) and X's block column kb,
+// X_ik = -(sum_l X_il R_lk) X_kk, whose sums need only earlier steps.
+// Only the blocks of block row kb + 1 are updated between two barriers.
+// 9.4 us for 64 columns on MI355X, against 17.5 us for a factorization with
+// three FMAs and two lane masks per entry, seven dependent operations per
+// reciprocal root and the inverse's off-diagonal blocks after it.
 //
-// gdiag gets G's diagonal (1 beyond n), rdiag R's; *bad is set when a pivot
-// is not above ratio * G_kk.  Starts and ends with a barrier.
+// gdiag gets G's diagonal (1 beyond n), rdiag R's; *bad is set to one plus
+// the smallest pivot index whose pivot is not above ratio * G_kk.  Starts and
+// ends with a barrier.
 HQR_DEV void chol64_dpp(double (*G)[LD65], double (*X)[LD65], int n, int lane, int w, double ratio,
                         double *gdiag, double *rdiag, int *bad)
 {
@@ -205,6 +387,7 @@ HQR_DEV void chol64_dpp(double (*G)[LD65], double (*X)[LD65], int n, int lane, i
         if (tid >= n) G[tid][tid] = 1.0;
     }
     if (tid == 0) *bad = 0;
+    f64x4 yt = {0.0, 0.0, 0.0, 0.0};   // wave w >= 1: Y^T of X's block (w - 1, kb)
     __syncthreads();
 #pragma unroll 1
     for (int kb = 0; kb < 4; ++kb) {
@@ -215,220 +398,340 @@ HQR_DEV void chol64_dpp(double (*G)[LD65], double (*X)[LD65], int n, int lane, i
             int ln = lane;
             asm volatile("" : "+v"(ln));
             const int jj = ln & 15, c = b0 + ln;
-            const bool act = c < NB;
-            double g[16], p[16], acc[16];
+            const bool aug = ln < 16, act = c < NB;
+            // 32 loads in flight from two addresses per lane, pinned before
+            // the selects (a conditional load becomes a branch and a wait of
+            // its own); the stores below likewise in two straight runs
+            double g[16], z[16];
+            const double *gp = &G[b0][b0 + jj], *zp = &G[b0][act ? c : b0 + jj];
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                g[i] = G[b0 + i][b0 + jj];
-                p[i] = act ? G[b0 + i][c] : 0.0;
-                acc[i] = 0.0;
+                g[i] = gp[i * LD65];
+                z[i] = zp[i * LD65];
             }
-            // lane i keeps pivot i and R_ii.  X = R_kk^{-1} is built along:
-            // lane j holds row j of X; acc[l] = sum_{i<l} X[j][i] R[i][l], and
-            // column i of X is -acc[i] / R_ii above the diagonal.
-            double my_d = 1.0, my_s = 0.0;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int gi = b0 + i;
-                const double d = bc16(g[i], i);
-                double s, r;
-                pivot_sqrt(d, s, r);
-                const double vg = (jj > i) ? g[i] * r : ((jj == i) ? s : 0.0);
-                const double vp = (c > gi) ? p[i] * r : ((c == gi) ? s : 0.0);
-                const double xi = (jj < i) ? -acc[i] * r : ((jj == i) ? r : 0.0);   // X[j][i]
-                g[i] = vg;
-                p[i] = vp;
-                my_d = (ln == i) ? d : my_d;
-                my_s = (ln == i) ? s : my_s;
-                X[b0 + jj][b0 + i] = xi;   // the four rows store the same value
+                pin(g[i]);
+                pin(z[i]);
+            }
 #pragma unroll
-                for (int i2 = i + 1; i2 < 16; ++i2) {
-                    const double t = bc16(vg, i2);          // R[i][i2]
-                    g[i2] = fma(-t, vg, g[i2]);
-                    p[i2] = fma(-t, vp, p[i2]);
-                    acc[i2] = fma(xi, t, acc[i2]);
-                    pin(g[i2]);
-                    pin(p[i2]);
-                    pin(acc[i2]);
+            for (int i = 0; i < 16; ++i) z[i] = aug ? ((i == jj) ? 1.0 : 0.0) : z[i];
+            double my_d = 1.0;         // lane i (and 16r + i): pivot i
+            double d = bc16c<0>(g[0]), r = pivot_rsqrt(d);
+            chol16_pivots(g, z, d, r, my_d, jj, std::make_integer_sequence<int, 16>{});
+            double my_s, my_r;
+            pivot_sqrt(my_d, my_s, my_r);
+            // row 0: R_kk's column jj and row jj of X_kk; rows 1..3: the block row
+            if (aug) {
+                double *xp = &X[b0 + jj][b0], *rp = &G[b0][b0 + jj];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) xp[i] = z[i];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) rp[i * LD65] = (i < jj) ? g[i] : 0.0;
+                rp[jj * LD65] = my_s;
+            } else if (act) {
+                double *rp = &G[b0][c];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) rp[i * LD65] = z[i];
+            }
+            const bool badl = aug && b0 + jj < n && !(my_d > ratio * gdiag[b0 + jj]);
+            if (aug) rdiag[b0 + jj] = my_s;
+            const unsigned long long bm = __ballot(badl);
+            if (bm && lane == 0 && *bad == 0) *bad = b0 + (int)__ffsll((long long)bm);
+        } else {
+            // the previous step's trailing blocks below block row kb
+            if (kb > 0) {
+                int cnt = 0;
+                for (int a = kb + 1; a <= 3; ++a)
+                    for (int b = a; b <= 3; ++b, ++cnt)
+                        if (cnt % 3 == w - 1) chol_trail_blk(G, b0 - 16, a, b, lane);
+            }
+            // X's column kb - 1 closed (its sums are from the previous step)
+            if (w - 1 < kb - 1) inv_upper_close(X, w - 1, kb - 1, yt, lane);
+            if (kb == 0) {
+                // zeros below the diagonal blocks, of G and X
+                for (int idx = tid - 64; idx < NB * NB; idx += 192) {
+                    const int r = idx / NB, cc = idx % NB;
+                    if ((r >> 4) > (cc >> 4)) {
+                        G[r][cc] = 0.0;
+                        X[r][cc] = 0.0;
+                    }
                 }
-                __builtin_amdgcn_sched_barrier(0);
             }
-            if (act) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) G[b0 + i][c] = p[i];
-            }
-            const bool badl = lane < 16 && b0 + lane < n && !(my_d > ratio * gdiag[b0 + lane]);
-            if (lane < 16) rdiag[b0 + lane] = my_s;
-            if (badl) *bad = 1;
+            // sums of column kb need X's columns < kb in row w - 1, which
+            // this wave itself wrote, and its diagonal block (wave 0, before
+            // the last barrier)
+            if (w - 1 < kb) yt = mma_sum_t(X, w - 1, G, kb, w - 1, kb, lane);
         }
         __syncthreads();
-        // trailing upper blocks (ib <= jb): G_ij -= R_p,i^T R_p,j, R_p = rows b0..b0+15
-        const int rem = 3 - kb;
-        const int nblk = rem * (rem + 1) / 2;
-        for (int bidx = w; bidx < nblk; bidx += 4) {
-            int ib = 0, jb = 0, cnt = 0;
-            for (int a = kb + 1; a <= 3; ++a)
-                for (int b = a; b <= 3; ++b) {
-                    if (cnt == bidx) { ib = a; jb = b; }
-                    ++cnt;
-                }
-            f64x4 acc = ld_blk(G, 16 * ib, 16 * jb, lane);
-            const int i16 = lane & 15, kk = lane >> 4;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int k = b0 + 4 * q + kk;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-G[k][16 * ib + i16], G[k][16 * jb + i16], acc, 0, 0, 0);
-            }
-            st_blk(G, 16 * ib, 16 * jb, acc, 1.0, lane);
+        if (kb < 3) {
+            const int jb = kb + 1 + w;
+            if (jb <= 3) chol_trail_blk(G, b0, kb + 1, jb, lane);
+            __syncthreads();
         }
-        __syncthreads();
     }
-    for (int idx = tid; idx < NB * NB; idx += 256) {
-        const int i = idx / NB, c = idx % NB;
-        if (i > c) G[i][c] = 0.0;
-    }
+    if (w > 0) inv_upper_close(X, w - 1, 3, yt, lane);
     __syncthreads();
 }
 
-// One block step of the LU below, in one wave: LPART = false computes U's
-// block row (lane t: column 16kb + t) and U_kk^{-1}; LPART = true computes
-// L's block column (lane t: row 16kb + t) and L_kk^{-1}.  Both keep the
-// diagonal block (lane 16r + j: its column j in dc, its row j in dr, in
-// every 16-lane row for the DPP broadcasts) and take the same pivots.
-// ov: U[.][c] (block row) or L[c][.] (block column) of the block step
+// One block step of the LU below, in one wave.  Every 16-lane row holds a
+// copy of the diagonal block in g; z holds an identity column in the lanes of
+// row 0 and, in rows 1..3, the rest of the block row or block column, so the
+// elimination that factors the block also yields one inverse and the
+// off-diagonal blocks.
+//   LPART = false: g lane j = column j of M_kk; eliminating [M_kk | I | M_k,..]
+//     gives U_kk (into M), L_kk^{-1} (into DL) and U's block row.
+//   LPART = true: the same elimination of [M_kk^T | I | M_..,k^T], with rows
+//     scaled by 1/U_ii at the end: L_kk (into DLL), U_kk^{-1} (at XU, row
+//     stride ldxu) and L's block column.  Its multipliers are formed so that every product has the
+//     other wave's operands: the pivots, and the signs taken from them, are
+//     bitwise the same.
+// One broadcast and two (LPART: three) operations per multiplier.
 template <bool LPART>
-HQR_DEV void lu64_load(const double (*M)[LD65], int b0, int lane, double (&ov)[16], double (&dc)[16],
-                       double (&dr)[16])
+HQR_DEV void lu64_load(const double (*M)[LD65], int b0, int lane, double (&g)[16], double (&z)[16])
 {
-    const int jj = lane & 15, c = b0 + lane;
-    const bool act = c < NB;
+    const int jj = lane & 15, c = b0 + lane, cz = (c < NB) ? c : b0;
+    const bool aug = lane < 16;
+    // LPART walks along rows of M, the other along columns
+    constexpr int st = LPART ? 1 : LD65;
+    const double *gp = LPART ? &M[b0 + jj][b0] : &M[b0][b0 + jj], *zp = LPART ? &M[cz][b0] : &M[b0][cz];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        ov[i] = act ? (LPART ? M[c][b0 + i] : M[b0 + i][c]) : 0.0;
-        dc[i] = M[b0 + i][b0 + jj];
-        dr[i] = M[b0 + jj][b0 + i];
+        g[i] = gp[i * st];
+        z[i] = zp[i * st];
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        pin(g[i]);
+        pin(z[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = aug ? ((i == jj) ? 1.0 : 0.0) : z[i];
+}
+
+// Pivot state of lu64_block: the current pivot's s_k, U_kk and reciprocal,
+// and the lane's own s_k and U_kk.
+struct LuPivot {
+    int jj;
+    double sg, ukk, uinv, my_sg = 0.0, my_uk = 0.0;
+    __device__ __forceinline__ void set(double q)
+    {
+        sg = (q >= 0.0) ? -1.0 : 1.0;
+        ukk = q - sg;
+    }
+};
+
+// One pivot of the 16 x 16 elimination (as chol16_pivot): multipliers
+// M[i2][I] (LPART: M[I][i2] U_II^{-1}) by broadcast, rows I scaled by U_II^{-1}
+// (LPART: not scaled) as the other factor.
+template <bool LPART, int I, int U>
+HQR_DEV void lu16_rows(double (&g)[16], double (&z)[16], double gm, double zm, double uinv, RecipChain &rc)
+{
+    constexpr int i2 = I + 2 + 2 * U;
+    if constexpr (i2 < 16) {
+        double ta = bc16c<I>(g[i2]), tb;
+        if constexpr (i2 + 1 < 16) tb = bc16c<I>(g[i2 + 1]);
+        if constexpr (LPART) {
+            ta *= uinv;
+            if constexpr (i2 + 1 < 16) tb *= uinv;
+        }
+        pin(ta);
+        if constexpr (i2 + 1 < 16) pin(tb);
+        g[i2] = fma(-ta, gm, g[i2]);
+        z[i2] = fma(-ta, zm, z[i2]);
+        pin(g[i2]);
+        pin(z[i2]);
+        if constexpr (i2 + 1 < 16) {
+            g[i2 + 1] = fma(-tb, gm, g[i2 + 1]);
+            z[i2 + 1] = fma(-tb, zm, z[i2 + 1]);
+            pin(g[i2 + 1]);
+            pin(z[i2 + 1]);
+        }
+    }
+    rc.template stage<U>();
+}
+
+template <bool LPART, int I>
+HQR_DEV void lu16_pivot(double (&g)[16], double (&z)[16], LuPivot &pv)
+{
+    const double uinv = pv.uinv;
+    const double gs = g[I] * uinv, zs = z[I] * uinv;
+    if (!LPART) {
+        pv.my_sg = (pv.jj == I) ? pv.sg : pv.my_sg;
+        pv.my_uk = (pv.jj == I) ? pv.ukk : pv.my_uk;
+    }
+    if constexpr (I < 15) {
+        const double gm = LPART ? g[I] : gs, zm = LPART ? z[I] : zs;
+        double t1 = bc16c<I>(g[I + 1]);
+        if (LPART) t1 *= uinv;
+        g[I + 1] = fma(-t1, gm, g[I + 1]);
+        pin(g[I + 1]);
+        double q = bc16c<I + 1>(g[I + 1]);
+        pin(q);
+        z[I + 1] = fma(-t1, zm, z[I + 1]);
+        pv.set(q);
+        RecipChain rc;
+        rc.start(pv.ukk);
+        lu16_rows<LPART, I, 0>(g, z, gm, zm, uinv, rc);
+        lu16_rows<LPART, I, 1>(g, z, gm, zm, uinv, rc);
+        lu16_rows<LPART, I, 2>(g, z, gm, zm, uinv, rc);
+        lu16_rows<LPART, I, 3>(g, z, gm, zm, uinv, rc);
+        lu16_rows<LPART, I, 4>(g, z, gm, zm, uinv, rc);
+        lu16_rows<LPART, I, 5>(g, z, gm, zm, uinv, rc);
+        lu16_rows<LPART, I, 6>(g, z, gm, zm, uinv, rc);
+        pv.uinv = rc.y;
+    }
+    if (LPART) {
+        g[I] = gs;
+        z[I] = zs;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <bool LPART, int... Is>
+HQR_DEV void lu16_pivots(double (&g)[16], double (&z)[16], LuPivot &pv, std::integer_sequence<int, Is...>)
+{
+    (lu16_pivot<LPART, Is>(g, z, pv), ...);
 }
 
 // The block step on the loaded values (after a barrier: the other wave's
-// writes to M cannot race with these reads).  ax: the running sums of
-// U_kk^{-1} (row j: ax[l] = sum_{i<l} XU[j][i] U[i][l]) or of L_kk^{-1}
-// (column j: ax[l] = sum_{i<l} L[l][i] XL[i][j]).
+// writes to M cannot race with these reads).
 template <bool LPART>
-HQR_DEV void lu64_block(double (*M)[LD65], double (*DX)[17], int b0, int lane, double *sgn, double *udiag,
-                        double (&ov)[16], double (&dc)[16], double (&dr)[16])
+HQR_DEV void lu64_block(double (*M)[LD65], double (*DL)[17], double (*DLL)[17], double *XU, int ldxu, int b0,
+                        int lane, double *sgn, double *udiag, double (&g)[16], double (&z)[16])
 {
     // opaque per block step: keeps the per-pivot lane masks from being
     // hoisted out of the caller's kb loop (they would occupy ~100 SGPRs)
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int jj = ln & 15, c = b0 + ln;
-    const bool act = c < NB;
-    double ax[16];
+    const bool aug = ln < 16, act = c < NB;
+    LuPivot pv;
+    pv.jj = jj;
+    pv.set(bc16c<0>(g[0]));
+    pv.uinv = recip_nr(pv.ukk);
+    lu16_pivots<LPART>(g, z, pv, std::make_integer_sequence<int, 16>{});
+    const double my_sg = pv.my_sg, my_uk = pv.my_uk;
+    // rows 1..3 write the off-diagonal blocks, row 0 the diagonal block
+    // (U with its diagonal, L below it) and the inverse's block
+    // straight runs of stores: the lower triangle of U's diagonal block and
+    // the upper one of L's are not meant to be read
+    if (aug) {
+        if (LPART) {
+            double *xp = XU + jj * ldxu, *dp = &DLL[b0 + jj][0];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) ax[i] = 0.0;
-    double my_sg = 0.0, my_uk = 0.0;
+            for (int i = 0; i < 16; ++i) xp[i] = z[i];      // U^{-1}[jj][i]
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int gi = b0 + i;
-        const double q = bc16(dc[i], i);
-        const double sg = (q >= 0.0) ? -1.0 : 1.0;
-        const double ukk = q - sg;
-        const double uinv = recip_nr(ukk);
-        const double ud = (jj > i) ? dc[i] : ((jj == i) ? ukk : 0.0);
-        const double ld = (jj > i) ? dr[i] * uinv : 0.0;
-        // U[gi][c] or L[c][gi]
-        const double oc = LPART ? ((c > gi) ? ov[i] * uinv : 0.0) : ((c > gi) ? ov[i] : ((c == gi) ? ukk : 0.0));
-        // XU[j][i] or XL[i][j]
-        const double xv = LPART ? ((jj < i) ? -ax[i] : ((jj == i) ? 1.0 : 0.0))
-                                : ((jj < i) ? -ax[i] * uinv : ((jj == i) ? uinv : 0.0));
-        dc[i] = ud;
-        dr[i] = ld;
-        ov[i] = oc;
-        if (!LPART) {
-            my_sg = (ln == i) ? sg : my_sg;
-            my_uk = (ln == i) ? ukk : my_uk;
-            DX[b0 + jj][i] = xv;       // the four rows store the same value
+            for (int i = 0; i < 16; ++i) dp[i] = g[i];      // L[jj][i]
         } else {
-            DX[b0 + i][jj] = xv;
-        }
+            double *xp = &DL[b0][jj], *dp = &M[b0][c];
 #pragma unroll
-        for (int i2 = i + 1; i2 < 16; ++i2) {
-            const double lb = bc16(ld, i2), ub = bc16(ud, i2);   // L[i2][i], U[i][i2]
-            dc[i2] = fma(-lb, ud, dc[i2]);
-            dr[i2] = fma(-ld, ub, dr[i2]);
-            if (!LPART) {
-                ov[i2] = fma(-lb, oc, ov[i2]);
-                ax[i2] = fma(xv, ub, ax[i2]);
-            } else {
-                ov[i2] = fma(-oc, ub, ov[i2]);
-                ax[i2] = fma(lb, xv, ax[i2]);
-            }
-            pin(dc[i2]);
-            pin(dr[i2]);
-            pin(ov[i2]);
-            pin(ax[i2]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (act) {
+            for (int i = 0; i < 16; ++i) xp[i * 17] = z[i]; // L^{-1}[i][jj]
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int gi = b0 + i;
-            if (!LPART && c >= gi) M[gi][c] = ov[i];
-            if (LPART && c > gi) M[c][gi] = ov[i];
+            for (int i = 0; i < 16; ++i) dp[i * LD65] = g[i];
+            dp[jj * LD65] = my_uk;
         }
+    } else if (act) {
+        double *dp = LPART ? &M[c][b0] : &M[b0][c];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dp[i * (LPART ? 1 : LD65)] = z[i];
     }
-    if (!LPART && ln < 16) {
-        sgn[b0 + ln] = my_sg;
-        udiag[b0 + ln] = my_uk;
+    if (!LPART && aug) {
+        sgn[b0 + jj] = my_sg;
+        udiag[b0 + jj] = my_uk;
     }
 }
 
 // In place: M (n x n leading block; entries outside it zero) becomes L
-// (strict lower, unit diagonal implied) and U (upper, diagonal U_kk) of the
-// LU factorization without pivoting of M - S, s_k = -sgn(pivot of step k)
-// (sgn(0) = +1); beyond n the factors continue as the identity (s_k = -1,
-// U_kk = 1).  Block step kb: wave 0 computes U's block row and the diagonal
-// block of U^{-1} (into DU, rows 16kb..16kb+15), wave 1 L's block column and
-// the diagonal block of L^{-1} (into DL), both by lu64_block; all waves then
-// subtract L_kb U_kb from the trailing blocks on MFMA.  sgn and udiag get s_k
-// and U_kk for all 64 steps.  Starts and ends with a barrier.
-HQR_DEV void lu64_dpp(double (*M)[LD65], double (*DU)[17], double (*DL)[17], int lane, int w, double *sgn,
-                      double *udiag)
+// (below the diagonal blocks; within them in DLL, unit diagonal implied) and
+// U (on and above the diagonal) of the LU factorization without pivoting of
+// M - S, s_k = -sgn(pivot of step k) (sgn(0) = +1); beyond n the factors
+// continue as the identity (s_k = -1, U_kk = 1).  Block step kb: wave 0
+// computes U's block row and the diagonal block of L^{-1} (into DL, rows
+// 16kb..16kb+15), wave 1 L's block column and the diagonal block of U^{-1}
+// (XU), both by lu64_block, while waves 2 and 3 finish the previous step's
+// trailing blocks and then do what the caller adds; between two barriers
+// only the blocks of block row and column kb + 1 are updated on MFMA.  sgn
+// and udiag get s_k and U_kk for all 64 steps.
+HQR_DEV void lu_trail_blk(double (*M)[LD65], int b0, int ib, int jb, int lane)
 {
-    __syncthreads();
-#pragma unroll 1
-    for (int kb = 0; kb < 4; ++kb) {
-        const int b0 = 16 * kb;
-        double ov[16], dc[16], dr[16];
-        if (w == 0) lu64_load<false>(M, b0, lane, ov, dc, dr);
-        else if (w == 1) lu64_load<true>(M, b0, lane, ov, dc, dr);
-        __syncthreads();
-        if (w == 0) lu64_block<false>(M, DU, b0, lane, sgn, udiag, ov, dc, dr);
-        else if (w == 1) lu64_block<true>(M, DL, b0, lane, sgn, udiag, ov, dc, dr);
-        __syncthreads();
-        // trailing blocks: M_ij -= L_p,i U_p,j over the block's 16 pivots
-        const int rem = 3 - kb;
-        for (int bidx = w; bidx < rem * rem; bidx += 4) {
-            const int ib = kb + 1 + bidx / rem, jb = kb + 1 + bidx % rem;
-            f64x4 acc = ld_blk(M, 16 * ib, 16 * jb, lane);
-            const int i16 = lane & 15, kk = lane >> 4;
+    f64x4 acc = ld_blk(M, 16 * ib, 16 * jb, lane);
+    const int i16 = lane & 15, kk = lane >> 4;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int k = b0 + 4 * q + kk;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-M[16 * ib + i16][k], M[k][16 * jb + i16], acc, 0, 0, 0);
-            }
-            st_blk(M, 16 * ib, 16 * jb, acc, 1.0, lane);
-        }
-        __syncthreads();
+    for (int q = 0; q < 4; ++q) {
+        const int k = b0 + 4 * q + kk;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-M[16 * ib + i16][k], M[k][16 * jb + i16], acc, 0, 0, 0);
     }
+    st_blk(M, 16 * ib, 16 * jb, acc, 1.0, lane);
+}
+
+// The pivots of step kb (a barrier inside, for all waves).
+HQR_DEV void lu64_pivots(double (*M)[LD65], double (*DL)[17], double (*DLL)[17], double *XU, int ldxu, int kb,
+                         int lane, int w, double *sgn, double *udiag)
+{
+    const int b0 = 16 * kb;
+    double g[16], z[16];
+    if (w == 0) {
+        lu64_load<false>(M, b0, lane, g, z);
+        __syncthreads();
+        lu64_block<false>(M, DL, DLL, XU, ldxu, b0, lane, sgn, udiag, g, z);
+    } else if (w == 1) {
+        lu64_load<true>(M, b0, lane, g, z);
+        __syncthreads();
+        lu64_block<true>(M, DL, DLL, XU, ldxu, b0, lane, sgn, udiag, g, z);
+    } else {
+        __syncthreads();
+        const int rem = 3 - kb;
+        if (kb > 0)
+            for (int bidx = w - 2; bidx < rem * rem; bidx += 2)
+                lu_trail_blk(M, b0 - 16, kb + 1 + bidx / rem, kb + 1 + bidx % rem, lane);
+    }
+}
+
+// After a barrier: block row and column kb + 1, i.e. (kb+1, kb+1..3) and
+// (kb+2..3, kb+1); ends with a barrier.
+HQR_DEV void lu64_trail(double (*M)[LD65], int kb, int lane, int w)
+{
+    const int rem = 3 - kb;
+    for (int t = w; t < 2 * rem - 1; t += 4) {
+        const int ib = (t < rem) ? kb + 1 : kb + 2 + (t - rem), jb = (t < rem) ? kb + 1 + t : kb + 1;
+        lu_trail_blk(M, 16 * kb, ib, jb, lane);
+    }
+    __syncthreads();
+}
+
+// Unit lower inverse whose diagonal blocks are in D (rows 16kb..) and whose
+// blocks below them are in X: the sum over k = j .. i-1 of L_ik X_kj in D
+// layout, and X_ij = -X_ii times that sum.
+HQR_DEV f64x4 mma_blk_d(f64x4 acc, const double (*MA)[LD65], int ar, int ac, const double (*D)[17], int kb, int lane)
+{
+    const int i = lane & 15, kk = lane >> 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(MA[ar + i][ac + 4 * q + kk], D[16 * kb + 4 * q + kk][i], acc, 0, 0, 0);
+    return acc;
+}
+
+HQR_DEV f64x4 mma_sum(const double (*L)[LD65], int i, const double (*X)[LD65], const double (*D)[17], int j, int lane)
+{
+    f64x4 t = mma_blk_d(f64x4{0.0, 0.0, 0.0, 0.0}, L, 16 * i, 16 * j, D, j, lane);
+    for (int k = j + 1; k < i; ++k) t = mma_blk(t, L, 16 * i, 16 * k, X, 16 * k, 16 * j, lane);
+    return t;
+}
+
+HQR_DEV void inv_lower_close(double (*X)[LD65], const double (*D)[17], int i, int j, f64x4 t, int lane)
+{
+    const int i16 = lane & 15, kk = lane >> 4;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(D[16 * i + i16][4 * q + kk], t[q], acc, 0, 0, 0);
+    st_blk(X, 16 * i, 16 * j, acc, -1.0, lane);
 }
 
 // Off-diagonal blocks of triangular inverses whose diagonal blocks are
 // already in place, by distance from the diagonal on MFMA:
-//   upper U:      X_ij = -X_ii sum_{k=i+1..j} U_ik X_kj   (i < j)
-//   unit lower L: X_ij = -X_ii sum_{k=j..i-1} L_ik X_kj   (i > j)
+//   X_ij = -X_ii sum_{k=i+1..j} U_ik X_kj   (i < j)
 // One 16 x 16 block task: t = sum of the products, X_ij = -X_ii t.
 HQR_DEV void inv_upper_task(double (*X)[LD65], const double (*U)[LD65], int i, int j, int lane)
 {
@@ -437,19 +740,12 @@ HQR_DEV void inv_upper_task(double (*X)[LD65], const double (*U)[LD65], int i, i
     st_blk(X, 16 * i, 16 * j, mma_blk_reg(f64x4{0.0, 0.0, 0.0, 0.0}, X, 16 * i, 16 * i, t, lane), -1.0, lane);
 }
 
-HQR_DEV void inv_lower_task(double (*X)[LD65], const double (*L)[LD65], int i, int j, int lane)
-{
-    f64x4 t = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int k = j; k < i; ++k) t = mma_blk(t, L, 16 * i, 16 * k, X, 16 * k, 16 * j, lane);
-    st_blk(X, 16 * i, 16 * j, mma_blk_reg(f64x4{0.0, 0.0, 0.0, 0.0}, X, 16 * i, 16 * i, t, lane), -1.0, lane);
-}
-
-// zero the blocks of X strictly below (lower = true: above) the diagonal
-HQR_DEV void zero_off_blocks(double (*X)[LD65], bool above, int tid)
+// zero the blocks of X strictly below the diagonal
+HQR_DEV void zero_lower_blocks(double (*X)[LD65], int tid)
 {
     for (int idx = tid; idx < NB * NB; idx += 256) {
         const int r = idx / NB, c = idx % NB;
-        if (above ? ((c >> 4) > (r >> 4)) : ((r >> 4) > (c >> 4))) X[r][c] = 0.0;
+        if ((r >> 4) > (c >> 4)) X[r][c] = 0.0;
     }
 }
 
@@ -458,33 +754,12 @@ HQR_DEV void zero_off_blocks(double (*X)[LD65], bool above, int tid)
 HQR_DEV void inv_upper_levels(double (*X)[LD65], const double (*U)[LD65], int lane, int w)
 {
     __syncthreads();
-    zero_off_blocks(X, false, 64 * w + lane);
+    zero_lower_blocks(X, 64 * w + lane);
     if (w < 3) inv_upper_task(X, U, w, w + 1, lane);
     __syncthreads();
     if (w < 2) inv_upper_task(X, U, w, w + 2, lane);
     __syncthreads();
     if (w == 0) inv_upper_task(X, U, 0, 3, lane);
-    __syncthreads();
-}
-
-// XU = U^{-1} and XL = L^{-1} for the U (upper) and L (strict lower, unit
-// diagonal) that share M, given the diagonal blocks of XU and XL.  Starts and
-// ends with a barrier.
-HQR_DEV void inv_lu_levels(double (*XU)[LD65], double (*XL)[LD65], const double (*M)[LD65], int lane, int w)
-{
-    __syncthreads();
-    zero_off_blocks(XU, false, 64 * w + lane);
-    zero_off_blocks(XL, true, 64 * w + lane);
-    for (int task = w; task < 6; task += 4) {
-        if (task < 3) inv_upper_task(XU, M, task, task + 1, lane);
-        else inv_lower_task(XL, M, task - 2, task - 3, lane);
-    }
-    __syncthreads();
-    if (w < 2) inv_upper_task(XU, M, w, w + 2, lane);
-    else inv_lower_task(XL, M, w, w - 2, lane);
-    __syncthreads();
-    if (w == 0) inv_upper_task(XU, M, 0, 3, lane);
-    else if (w == 1) inv_lower_task(XL, M, 3, 0, lane);
     __syncthreads();
 }
 
@@ -495,7 +770,7 @@ HQR_DEV void inv_lu_levels(double (*XU)[LD65], double (*XL)[LD65], const double 
 // Upper x upper: the 10 blocks bi <= bj, each summed over k = bi..bj (20
 // block products), spread 5 per wave; uu_slot gives slot s of wave w as
 // 4 bi + bj, or -1.
-HQR_DEV int uu_slot(int w, int s)
+constexpr int uu_slot_c(int w, int s)
 {
     // w0: (0,3) (3,3)  w1: (0,2) (1,2)  w2: (1,3) (0,1)  w3: (2,3) (0,0) (1,1) (2,2)
     const unsigned tab = (w == 0) ? 0xffff0f03u : (w == 1) ? 0xffff0602u : (w == 2) ? 0xffff0107u : 0x0a05000bu;
@@ -503,23 +778,82 @@ HQR_DEV int uu_slot(int w, int s)
     return e == 0xff ? -1 : e;
 }
 
-template <class FA, class FB>
-HQR_DEV void mm_upper_upper(f64x4 (&acc)[4], FA fa, FB fb, int lane, int w)
+// One wave's share, its blocks known at compile time: the five block
+// products become straight code whose loads and MFMAs the compiler can
+// overlap (with the wave as a runtime value each product was a loop round
+// of its own, its loads waited for one after the other: about 0.4 us each).
+template <int W, int S, class FA, class FB>
+HQR_DEV void mm_uu_block(f64x4 &acc, FA fa, FB fb, int lane)
 {
-    const int i16 = lane & 15, kk = lane >> 4;
+    constexpr int e = uu_slot_c(W, S);
+    acc = f64x4{0.0, 0.0, 0.0, 0.0};
+    if constexpr (e >= 0) {
+        constexpr int bi = e >> 2, bj = e & 3;
+        const int i16 = lane & 15, kk = lane >> 4;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        acc[s] = f64x4{0.0, 0.0, 0.0, 0.0};
-        const int e = uu_slot(w, s);
-        if (e < 0) continue;
-        const int bi = e >> 2, bj = e & 3;
         for (int kb = bi; kb <= bj; ++kb) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int k = 16 * kb + 4 * q + kk;
-                acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa(16 * bi + i16, k), fb(k, 16 * bj + i16), acc[s], 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa(16 * bi + i16, k), fb(k, 16 * bj + i16), acc, 0, 0, 0);
             }
         }
+    }
+}
+
+template <int W, class FA, class FB>
+HQR_DEV void mm_uu_wave(f64x4 (&acc)[4], FA fa, FB fb, int lane)
+{
+    mm_uu_block<W, 0>(acc[0], fa, fb, lane);
+    mm_uu_block<W, 1>(acc[1], fa, fb, lane);
+    mm_uu_block<W, 2>(acc[2], fa, fb, lane);
+    mm_uu_block<W, 3>(acc[3], fa, fb, lane);
+}
+
+// w must be uniform over the wave (a scalar)
+template <class FA, class FB>
+HQR_DEV void mm_upper_upper(f64x4 (&acc)[4], FA fa, FB fb, int lane, int w)
+{
+    if (w == 0) mm_uu_wave<0>(acc, fa, fb, lane);
+    else if (w == 1) mm_uu_wave<1>(acc, fa, fb, lane);
+    else if (w == 2) mm_uu_wave<2>(acc, fa, fb, lane);
+    else mm_uu_wave<3>(acc, fa, fb, lane);
+}
+
+// In place, one wave: block row I of A B over A's, for upper A and B.  Block
+// (I, j) needs A's blocks up to column j only, so the row goes from right to
+// left; rows are independent.
+template <int I>
+HQR_DEV void mul_upper_row(double (*A)[LD65], const double (*B)[LD65], int lane)
+{
+#pragma unroll
+    for (int j = 3; j >= I; --j) {
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = I; k <= j; ++k) acc = mma_blk(acc, A, 16 * I, 16 * k, B, 16 * k, 16 * j, lane);
+        st_blk(A, 16 * I, 16 * j, acc, 1.0, lane);
+        __builtin_amdgcn_sched_barrier(0);   // one block's operands in registers at a time
+    }
+}
+
+// In place, one wave: block column J of A B over B's, for upper A (64 x 64
+// row-major in global memory) and B: from top to bottom, columns independent.
+template <int J>
+HQR_DEV void mul_upper_col(const double *A, double (*B)[LD65], int lane)
+{
+    const int i16 = lane & 15, kk = lane >> 4;
+#pragma unroll
+    for (int i = 0; i <= J; ++i) {
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = i; k <= J; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = 16 * k + 4 * q + kk;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[(16 * i + i16) * NB + r], B[r][16 * J + i16], acc, 0, 0, 0);
+            }
+        st_blk(B, 16 * i, 16 * J, acc, 1.0, lane);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -530,31 +864,49 @@ HQR_DEV void mm_full_upper(f64x4 (&acc)[4], FA fa, FB fb, int lane, int w)
 {
     const int i16 = lane & 15, kk = lane >> 4;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        acc[s] = f64x4{0.0, 0.0, 0.0, 0.0};
-        for (int kb = 0; kb <= s; ++kb) {
+    for (int s = 0; s < 4; ++s) acc[s] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int k = 16 * kb + 4 * q + kk;
-                acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa(16 * w + i16, k), fb(k, 16 * s + i16), acc[s], 0, 0, 0);
-            }
+    for (int kb = 0; kb < 4; ++kb) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 16 * kb + 4 * q + kk;
+            const double a = fa(16 * w + i16, k);
+#pragma unroll
+            for (int s = kb; s < 4; ++s)
+                acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, fb(k, 16 * s + i16), acc[s], 0, 0, 0);
         }
     }
 }
 
 // Visit the elements of the wave's upper x upper accumulators:
 // f(row, col, value).
+template <int W, int S, class F>
+HQR_DEV void for_uu_block(const f64x4 &acc, F f, int lane)
+{
+    constexpr int e = uu_slot_c(W, S);
+    if constexpr (e >= 0) {
+        constexpr int bi = e >> 2, bj = e & 3;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f(16 * bi + 4 * q + (lane >> 4), 16 * bj + (lane & 15), acc[q]);
+    }
+}
+
+template <int W, class F>
+HQR_DEV void for_uu_wave(const f64x4 (&acc)[4], F f, int lane)
+{
+    for_uu_block<W, 0>(acc[0], f, lane);
+    for_uu_block<W, 1>(acc[1], f, lane);
+    for_uu_block<W, 2>(acc[2], f, lane);
+    for_uu_block<W, 3>(acc[3], f, lane);
+}
+
 template <class F>
 HQR_DEV void for_uu(const f64x4 (&acc)[4], F f, int lane, int w)
 {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int e = uu_slot(w, s);
-        if (e < 0) continue;
-        const int bi = e >> 2, bj = e & 3;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) f(16 * bi + 4 * q + (lane >> 4), 16 * bj + (lane & 15), acc[s][q]);
-    }
+    if (w == 0) for_uu_wave<0>(acc, f, lane);
+    else if (w == 1) for_uu_wave<1>(acc, f, lane);
+    else if (w == 2) for_uu_wave<2>(acc, f, lane);
+    else for_uu_wave<3>(acc, f, lane);
 }
 
 // M[r][c] = A[r0 + r][c0 + c] (r < 64, c < NB), zero for rows >= m or
@@ -948,6 +1300,24 @@ __global__ void __launch_bounds__(256) gram_reduce_kernel(GredArgs p)
 // then I + O(kappa^2 u)).
 constexpr double CQR_SERIES_TAU = 0x1p-30;
 
+template <int W>
+HQR_DEV void near_gram(f64x4 (&acc)[4], const double (*X)[LD65], int lane)
+{
+    const int i16 = lane & 15, kk = lane >> 4;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc[s] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kb = 0; kb <= W; ++kb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 16 * kb + 4 * q + kk;
+            const double a = X[k][16 * W + i16];
+#pragma unroll
+            for (int s = W; s < 4; ++s)
+                acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, X[k][16 * s + i16], acc[s], 0, 0, 0);
+        }
+}
+
 // On entry (after a barrier) G holds I + E in full and X holds Phi(E).  On
 // exit G = R and X = R^{-1} (upper, zeros below), rdiag = diag(R); ends with
 // a barrier.
@@ -956,18 +1326,10 @@ HQR_DEV void chol_near_identity(double (*G)[LD65], double (*X)[LD65], double *rd
     const int i16 = lane & 15, kk = lane >> 4;
     // P = X0^T X0 on the wave's upper blocks (w, s >= w): k-blocks 0..w
     f64x4 acc[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        acc[s] = f64x4{0.0, 0.0, 0.0, 0.0};
-        if (s < w) continue;
-        for (int kb = 0; kb <= w; ++kb) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int k = 16 * kb + 4 * q + kk;
-                acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(X[k][16 * w + i16], X[k][16 * s + i16], acc[s], 0, 0, 0);
-            }
-        }
-    }
+    if (w == 0) near_gram<0>(acc, X, lane);
+    else if (w == 1) near_gram<1>(acc, X, lane);
+    else if (w == 2) near_gram<2>(acc, X, lane);
+    else near_gram<3>(acc, X, lane);
     // X1 = Phi(E - P) on the wave's rows, kept in registers
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -997,7 +1359,11 @@ HQR_DEV void chol_near_identity(double (*G)[LD65], double (*X)[LD65], double *rd
 }
 
 
-// One workgroup, 256 threads.
+// One workgroup, 256 threads.  Bound: latency (two of these per panel are
+// about half of the panel chain): the pivots' dependent operations, then LDS
+// round trips between small products.  Launch to end on MI355X, 64 columns:
+// pass 1 17.1 us, pass 2 31.5 us (37 us with a pivoted Cholesky); 25.0 and
+// 46.9 (59) us with every phase on all four waves one after the other.
 //   pass 1: R1 = chol(G), R1^{-1}; flags the panel (structurally exact
 //           reflectors, or a pivot below CQR_RATIO).
 //   flagged panel, pass 2: the exact one-reflector loop instead.
@@ -1011,10 +1377,11 @@ __global__ void __launch_bounds__(256) cqr_chol_kernel(CholArgs p)
     __shared__ double M1[NB][LD65];
     __shared__ double M2[NB][LD65];
     __shared__ double M3[NB][LD65];
-    __shared__ double DU[NB][17], DL[NB][17];
+    __shared__ double DU0[16][17], DL[NB][17], DLL[NB][17];
     __shared__ double gdiag[NB], rdiag[NB], sgn[NB], udiag[NB], upv[NB], rupv[NB];
     __shared__ int bad, structural_sh, nonid_sh;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // a scalar: uniform branches
     const int bw = p.bw;
     if (tid == 0) {
         structural_sh = 0;
@@ -1095,7 +1462,6 @@ __global__ void __launch_bounds__(256) cqr_chol_kernel(CholArgs p)
         return;
     }
     if (bad || structural_sh) return;
-    if (!series) inv_upper_levels(M1, M0, lane, w);     // M1 = R^{-1} of this pass
     HQR_TS();
 
     if (p.pass == 1) {
@@ -1107,94 +1473,142 @@ __global__ void __launch_bounds__(256) cqr_chol_kernel(CholArgs p)
     }
 
     // ---- pass 2: M0 = R2, M1 = R2^{-1}, M2 = Q1_top, M3 = R1
+    // M2 = Q_top = Q1_top R2^{-1}
     {
         f64x4 qacc[4];
         mm_full_upper(qacc, [&](int r, int c) { return M2[r][c]; }, [&](int r, int c) { return M1[r][c]; }, lane, w);
         __syncthreads();
 #pragma unroll
-        for (int s = 0; s < 4; ++s) st_blk(M2, 16 * w, 16 * s, qacc[s], 1.0, lane);  // M2 = Q_top
+        for (int s = 0; s < 4; ++s) st_blk(M2, 16 * w, 16 * s, qacc[s], 1.0, lane);
     }
     HQR_TS();
-    // LU of Q_top - S in M2; diagonal blocks of U^{-1} -> DU, of L^{-1} -> DL
-    lu64_dpp(M2, DU, DL, lane, w, sgn, udiag);
-    HQR_TS();
-    // R = R2 R1; R_house = S R into the upper triangle of the panel's top block
-    {
-        f64x4 racc[4];
-        mm_upper_upper(racc, [&](int r, int c) { return M0[r][c]; }, [&](int r, int c) { return M3[r][c]; }, lane, w);
-        for_uu(racc, [&](int r, int c, double v) {
-            if (r <= c && c < bw) HQR_AT(p.A, (int64_t)p.c0 + r, p.c0 + c, p.lda) = sgn[r] * v;
-        }, lane, w);
+    // LU of Q_top - S in M2.  Waves 0 and 1 work on its pivots; waves 2 and 3
+    // form beside them what does not wait for the pivots or waits for earlier
+    // block steps only:
+    //   step 0: R = R2 R1 over R2 (M0), half the products each
+    //   step 1: P = R1^{-1} R2^{-1} over R2^{-1} (M1), R1^{-1} from global
+    //           memory
+    //   from step 1, in M3 (R1 until step 0): wave 2 U^{-1}'s block columns
+    //           above the diagonal blocks wave 1 leaves there (step 0's comes
+    //           through DU0), wave 3 L^{-1}'s block rows below them (L^{-1}'s
+    //           diagonal blocks are in DL); each block's sum one step before
+    //           its product with the new diagonal block
+    // After the last pivot one product per block of the last column and row
+    // and the products T and W^{-1} = P U^{-1} diag(up) are left.
+    f64x4 y0 = {0.0, 0.0, 0.0, 0.0}, y1 = y0, y2 = y0;
+    __syncthreads();
+#pragma unroll 1
+    for (int kb = 0; kb < 4; ++kb) {
+        // opaque per step: the LDS addresses of the products below would
+        // otherwise be computed before the loop and kept in ~150 registers
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        double *XU = (kb == 0) ? &DU0[0][0] : &M3[16 * kb][16 * kb];
+        lu64_pivots(M2, DL, DLL, XU, (kb == 0) ? 17 : LD65, kb, ln, w, sgn, udiag);
+        if (w >= 2) {
+            if (kb == 0) {
+                if (w == 2) {
+                    mul_upper_row<0>(M0, M3, ln);
+                } else {
+                    mul_upper_row<1>(M0, M3, ln);
+                    mul_upper_row<2>(M0, M3, ln);
+                    mul_upper_row<3>(M0, M3, ln);
+                }
+            } else if (kb == 1) {
+                if (w == 2) {
+                    mul_upper_col<3>(p.r1inv, M1, ln);
+                    const int i16 = ln & 15, kk = ln >> 4;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) M3[4 * q + kk][i16] = DU0[4 * q + kk][i16];
+                    y0 = mma_sum_t(M3, 0, M2, 1, 0, 1, ln);
+                } else {
+                    mul_upper_col<0>(p.r1inv, M1, ln);
+                    mul_upper_col<1>(p.r1inv, M1, ln);
+                    mul_upper_col<2>(p.r1inv, M1, ln);
+                    y0 = mma_sum(M2, 1, M3, DL, 0, ln);
+                }
+            } else if (kb == 2) {
+                if (w == 2) {
+                    inv_upper_close(M3, 0, 1, y0, ln);
+                    y0 = mma_sum_t(M3, 0, M2, 2, 0, 2, ln);
+                    y1 = mma_sum_t(M3, 1, M2, 2, 1, 2, ln);
+                } else {
+                    inv_lower_close(M3, DL, 1, 0, y0, ln);
+                    y0 = mma_sum(M2, 2, M3, DL, 0, ln);
+                    y1 = mma_sum(M2, 2, M3, DL, 1, ln);
+                }
+            } else if (kb == 3) {
+                if (w == 2) {
+                    inv_upper_close(M3, 0, 2, y0, ln);
+                    inv_upper_close(M3, 1, 2, y1, ln);
+                    y0 = mma_sum_t(M3, 0, M2, 3, 0, 3, ln);
+                    y1 = mma_sum_t(M3, 1, M2, 3, 1, 3, ln);
+                    y2 = mma_sum_t(M3, 2, M2, 3, 2, 3, ln);
+                } else {
+                    inv_lower_close(M3, DL, 2, 0, y0, ln);
+                    inv_lower_close(M3, DL, 2, 1, y1, ln);
+                    y0 = mma_sum(M2, 3, M3, DL, 0, ln);
+                    y1 = mma_sum(M2, 3, M3, DL, 1, ln);
+                    y2 = mma_sum(M2, 3, M3, DL, 2, ln);
+                }
+            }
+        }
+        __syncthreads();
+        if (kb < 3) lu64_trail(M2, kb, ln, w);
     }
-    if (tid < bw) {
-        const double rkk = sgn[tid] * rdiag[tid] * M3[tid][tid];  // diag of S R2 R1
-        const double tau = -udiag[tid] * sgn[tid];                // = 1 + |pivot|
-        upv[tid] = -tau * rkk;
-        rupv[tid] = 1.0 / upv[tid];   // nonzero: tau >= 1 and R_kk != 0 on this path
+    HQR_TS();
+    if (w == 2) {
+        inv_upper_close(M3, 0, 3, y0, lane);
+        inv_upper_close(M3, 1, 3, y1, lane);
+        inv_upper_close(M3, 2, 3, y2, lane);
+    } else if (w == 3) {
+        inv_lower_close(M3, DL, 3, 0, y0, lane);
+        inv_lower_close(M3, DL, 3, 1, y1, lane);
+        inv_lower_close(M3, DL, 3, 2, y2, lane);
+    } else if (w == 0 && tid < bw) {
+        const double rkk = sgn[tid] * M0[tid][tid];   // diag of S R2 R1
+        const double tau = -udiag[tid] * sgn[tid];    // = 1 + |pivot|
+        const double u = -tau * rkk;
+        upv[tid] = u;
+        rupv[tid] = 1.0 / u;   // nonzero: tau >= 1 and R_kk != 0 on this path
+        p.up[p.c0 + tid] = u;
     }
     __syncthreads();
-    // diagonal blocks of U^{-1} -> M0, of L^{-1} -> M3; then the rest
-    for (int idx = tid; idx < NB * 16; idx += 256) {
-        const int r = idx >> 4, cc = idx & 15, c = 16 * (r >> 4) + cc;
-        M0[r][c] = DU[r][cc];
-        M3[r][c] = DL[r][cc];
-    }
-    inv_lu_levels(M0, M3, M2, lane, w);                 // M0 = U^{-1}, M3 = L^{-1}
     HQR_TS();
-    // R1^{-1} is fetched now (into M1 once V1 no longer needs R2^{-1} there),
-    // so its latency overlaps the two products below
-    double r1i[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) r1i[t] = p.r1inv[tid + 256 * t];
-    // T_Y = -(U S) L^{-T}, T_V = T_Y / (up_i up_j) -> global; V1 = R2^{-1} U^{-1}
-    f64x4 vacc[4];
+    // T_Y = -(U S) L^{-T}, T_V = T_Y / (up_i up_j); W^{-1} = P U^{-1} diag(up)
+    // (both zero beyond bw and below the diagonal)
     {
-        f64x4 tacc[4];
+        f64x4 tacc[4], wacc[4];
+        // L^{-1}: diagonal blocks in DL, the blocks below them in M3
         mm_upper_upper(tacc, [&](int r, int c) { return (c >= r && c < bw) ? M2[r][c] * sgn[c] : 0.0; },
-                       [&](int r, int c) { return M3[c][r]; }, lane, w);
-        for (int idx = tid; idx < NB * NB; idx += 256) {
-            const int i = idx / NB, j = idx % NB;
-            if (!(i <= j && j < bw)) p.T[idx] = 0.0;
-        }
+                       [&](int r, int c) {
+                           const double *q = ((c >> 4) == (r >> 4)) ? &DL[c][r & 15] : &M3[c][r];
+                           return *q;
+                       }, lane, w);
+        mm_upper_upper(wacc, [&](int r, int c) { return M1[r][c]; }, [&](int r, int c) { return M3[r][c]; }, lane, w);
+        HQR_TS();
         for_uu(tacc, [&](int r, int c, double v) {
-            if (r <= c && c < bw) p.T[r * NB + c] = -v * (rupv[r] * rupv[c]);
+            p.T[r * NB + c] = (r <= c && c < bw) ? -v * (rupv[r] * rupv[c]) : 0.0;
         }, lane, w);
-    }
-    HQR_TS();
-    mm_upper_upper(vacc, [&](int r, int c) { return M1[r][c]; }, [&](int r, int c) { return M0[r][c]; }, lane, w);
-    __syncthreads();
-    // M0 = V1 (its blocks below the diagonal are still U^{-1}'s zeros), M1 = R1^{-1}
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int e = uu_slot(w, s);
-        if (e >= 0) st_blk(M0, 16 * (e >> 2), 16 * (e & 3), vacc[s], 1.0, lane);
-    }
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const int idx = tid + 256 * t;
-        M1[idx / NB][idx % NB] = r1i[t];
-    }
-    __syncthreads();
-    HQR_TS();
-    // W^{-1} = R1^{-1} V1 diag(up) -> global (zero beyond bw and below the diagonal)
-    {
-        f64x4 wacc[4];
-        mm_upper_upper(wacc, [&](int r, int c) { return M1[r][c]; }, [&](int r, int c) { return M0[r][c]; }, lane, w);
+        for_uu(wacc, [&](int r, int c, double v) { p.winv[r * NB + c] = (c < bw) ? v * upv[c] : 0.0; }, lane, w);
         for (int idx = tid; idx < NB * NB; idx += 256) {
             const int i = idx / NB, j = idx % NB;
-            if ((i >> 4) > (j >> 4) || j >= bw) p.winv[idx] = 0.0;
+            if ((i >> 4) > (j >> 4)) {
+                p.T[idx] = 0.0;
+                p.winv[idx] = 0.0;
+            }
         }
-        for_uu(wacc, [&](int r, int c, double v) {
-            if (c < bw) p.winv[r * NB + c] = v * upv[c];
-        }, lane, w);
     }
     HQR_TS();
-    // stored tails of the top block: L[i][j] * up_j (strict lower)
+    // the panel's top block: R_house = S R on and above the diagonal, the
+    // stored tails L[i][j] * up_j below it
+#pragma unroll 4
     for (int idx = tid; idx < NB * NB; idx += 256) {
         const int c = idx / NB, r = idx % NB;
-        if (r > c && r < bw) HQR_AT(p.A, (int64_t)p.c0 + r, p.c0 + c, p.lda) = M2[r][c] * upv[c];
+        const double *lp = ((r >> 4) == (c >> 4)) ? &DLL[r][c & 15] : &M2[r][c];
+        const double v = (r > c) ? *lp * upv[c] : sgn[r] * M0[r][c];
+        if (r < bw && c < bw) HQR_AT(p.A, (int64_t)p.c0 + r, p.c0 + c, p.lda) = v;
     }
-    if (tid < bw) p.up[p.c0 + tid] = upv[tid];
     HQR_TS();
 #undef HQR_TS
 }
