@@ -1657,10 +1657,8 @@ int hqr_cholesky(int64_t n, double *S, int64_t lds, void *work, int64_t lwork, i
     } else if (lwork < (int64_t)need) {
         return HQR_ENOMEM;
     }
-    for (int64_t k0 = 0; k0 < n; k0 += 64) {
-        const int bw = (int)std::min<int64_t>(64, n - k0);
-        HQR_CK(k_chol_block(stream, S, lds, n, k0, bw, rinv, info));
-    }
+    HQR_CK(k_chol_first(stream, S, lds, n, rinv, info));
+    for (int64_t k0 = 0; k0 + 64 < n; k0 += 64) HQR_CK(k_chol_block(stream, S, lds, n, k0, 64, rinv, info));
     return 0;
 }
 
