@@ -60,16 +60,49 @@ struct VtxArgs {
 constexpr int VTX_COLS = 128;
 
 // ------------------------------------------------- T from G = V^T V and tau
-// One workgroup.  tau_k = -1/(up_k R_kk) (0 for identity reflectors);
+// One workgroup per panel: workgroup i takes columns [c0 + 64 i, +64) of the
+// bw columns from c0.  tau_k = -1/(up_k R_kk) (0 for identity reflectors);
 // T[j][j] = tau_j, T[0:j, j] = -tau_j T[0:j, 0:j] G[0:j, j].
 struct TArgs {
     const double *A;
     int64_t lda;
     const double *up;
     int c0, bw;
-    const double *wpart; // partials holding G in columns [0, bw)
+    const double *wpart; // partials holding G in columns [0, 64), panel after panel
     int nsplit, nxpad;
-    double *T;           // [NB][NB] row-major T[i][j]
+    size_t wstride;      // from one panel's partials to the next's
+    double *T;           // [panels][NB][NB] row-major T[i][j]
+};
+
+// ------------------------------------------- applying a stored factorization
+struct StoredGramArgs {
+    const double *A;
+    int64_t lda;
+    const double *up;
+    int64_t m, n;
+    double *gpart;       // [panels][splits][NB][NB] partial V^T V
+};
+
+// Columns one stored_step_kernel launch takes (one MFMA column tile).
+constexpr int SN_COLS = 16;
+
+struct StoredStepArgs {
+    const double *A;
+    int64_t lda;
+    const double *up;
+    double *B;
+    int64_t ldb;
+    int64_t m;
+    int nrhs;            // 1 .. SN_COLS
+    int64_t base;        // first row of part 0
+    int tiles;           // 64-row tiles per part
+    int cp, bwp;         // panel to finish (bwp 0: none)
+    int c0, bw;          // panel whose X = V^T B is formed next (bw 0: none)
+    int tmode;           // 0: W = T^T X (Q^T), 1: W = T X (Q)
+    const double *T;     // T of the panel to finish
+    const double *xin;   // [nparts][nrhs][NB] its X, by parts
+    int nparts;
+    double *xout;        // [parts][nrhs][NB]
 };
 
 // ------------------------------------------------ W' = T^T (sum of partials)
@@ -403,7 +436,7 @@ void prof_end(int cls, hipEvent_t e0, hipStream_t s);
 // hqr_blocked.hpp (k_blocked.hip)
 hipError_t k_panel_col(dim3 grid, hipStream_t s, const PanelArgs &a);
 hipError_t k_vtx(bool f32, bool with_v, dim3 grid, hipStream_t s, const VtxArgs &a);
-hipError_t k_tfactor(hipStream_t s, const TArgs &a);
+hipError_t k_tfactor(int panels, hipStream_t s, const TArgs &a);
 hipError_t k_wsolve(bool narrow, dim3 grid, hipStream_t s, const WArgs &a);
 hipError_t k_update(bool narrow, bool f32, dim3 grid, hipStream_t s, const UpdArgs &a);
 hipError_t k_diag_check(hipStream_t s, const double *A, int64_t lda, int64_t n, int *info);
@@ -458,6 +491,10 @@ hipError_t k_gemv_sub(hipStream_t s, const double *M, int64_t ldm, const double 
                       int64_t p);
 hipError_t k_copy_vec(hipStream_t s, const double *src, double *dst, int64_t n);
 hipError_t k_lse_info(hipStream_t s, int *info, const int *info_c, const int *info_r, int64_t p);
+
+// hqr_stored.hpp (k_stored.hip)
+hipError_t k_stored_gram(int panels, int nsplit, hipStream_t s, const StoredGramArgs &a);
+hipError_t k_stored_step(int parts, hipStream_t s, const StoredStepArgs &a);
 
 // hqr_chol.hpp (k_chol.hip): the first diagonal block of the Cholesky
 // factorization; one block row with the trailing update and the next diagonal

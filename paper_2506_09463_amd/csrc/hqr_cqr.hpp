@@ -1351,13 +1351,16 @@ __global__ void __launch_bounds__(256) xw_reduce_kernel(XwArgs p)
 // G[l][k] into every later column's sum once T[i][l] is final), then the
 // blocks above them by distance from the diagonal on MFMA
 // (inv_upper_levels).  Zero taus (identity reflectors, columns past bw) give
-// zero rows and columns.  One workgroup of 256 threads.
+// zero rows and columns.  One workgroup of 256 threads per panel.
 __global__ void __launch_bounds__(256) tfactor_kernel(TArgs p)
 {
     __shared__ double G[NB][LD65];
     __shared__ double Ts[NB][LD65];
     __shared__ double tau[NB];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int c0 = p.c0 + NB * (int)blockIdx.x, bw = min(NB, p.bw - NB * (int)blockIdx.x);
+    const double *wpart = p.wpart + (size_t)blockIdx.x * p.wstride;
+    double *T = p.T + (size_t)blockIdx.x * NB * NB;
     // G = the splits' partial V^T V summed in split order; a thread's 16
     // elements are loaded together for each split
     constexpr int EPT = NB * NB / 256;
@@ -1366,11 +1369,11 @@ __global__ void __launch_bounds__(256) tfactor_kernel(TArgs p)
     for (int e = 0; e < EPT; ++e) gs[e] = 0.0;
 #pragma unroll 4
     for (int q = 0; q < p.nsplit; ++q) {
-        const double *src = p.wpart + (size_t)q * NB * p.nxpad;
+        const double *src = wpart + (size_t)q * NB * p.nxpad;
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             const int idx = tid + 256 * e, i = idx / NB, j = idx - i * NB;
-            gs[e] += (i < p.bw && j < p.bw) ? src[(size_t)i * p.nxpad + j] : 0.0;
+            gs[e] += (i < bw && j < bw) ? src[(size_t)i * p.nxpad + j] : 0.0;
         }
     }
 #pragma unroll
@@ -1380,9 +1383,9 @@ __global__ void __launch_bounds__(256) tfactor_kernel(TArgs p)
     }
     if (tid < NB) {
         double t = 0.0;
-        if (tid < p.bw) {
-            const double u = p.up[p.c0 + tid];
-            const double rkk = HQR_AT(p.A, (int64_t)p.c0 + tid, p.c0 + tid, p.lda);
+        if (tid < bw) {
+            const double u = p.up[c0 + tid];
+            const double rkk = HQR_AT(p.A, (int64_t)c0 + tid, c0 + tid, p.lda);
             t = (u == 0.0) ? 0.0 : -1.0 / (u * rkk);
         }
         tau[tid] = t;
@@ -1403,7 +1406,7 @@ __global__ void __launch_bounds__(256) tfactor_kernel(TArgs p)
         for (int l = 0; l < 16; ++l) Ts[b0 + i][b0 + l] = trow[l];
     }
     inv_upper_levels(Ts, G, lane, w);
-    for (int idx = tid; idx < NB * NB; idx += 256) p.T[idx] = Ts[idx / NB][idx % NB];
+    for (int idx = tid; idx < NB * NB; idx += 256) T[idx] = Ts[idx / NB][idx % NB];
 }
 
 } // namespace hqr

@@ -416,8 +416,9 @@ static int apply_panel_block(const Plan &pl, const TrailBufs &tb, double *A, int
         t.wpart = tb.wpart;
         t.nsplit = nsplit_eff;
         t.nxpad = v.nxpad;
+        t.wstride = 0;
         t.T = tb.T;
-        HQR_CK(k_tfactor(s, t));
+        HQR_CK(k_tfactor(1, s, t));
     }
 
     const int ncols = ncA + nB;
@@ -934,6 +935,73 @@ static int get_work(const Plan &pl, void *work, int64_t lwork, hipStream_t s, Wo
     return 0;
 }
 
+// T of the leading npan stored panels into w.wp2 (64 x 64 each), in two
+// launches: partial V^T V by row splits (into w.wpart2), then one workgroup
+// per panel.  Both buffers are as wide as the whole matrix, so every panel's
+// part fits.  T does not depend on B: formed panel by panel it stood between
+// each panel's V^T B and its update (12 us a panel at 2047 x 1500).
+static int stored_t(const Plan &pl, const Work &w, const double *A, int64_t lda, const double *up, int npan,
+                    hipStream_t s)
+{
+    const int64_t tiles = (pl.m + 63) / 64;
+    const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)pl.nsplit_max, tiles, 512 / npan}));
+    const StoredGramArgs g{A, lda, up, pl.m, pl.n, w.wpart2};
+    HQR_CK(k_stored_gram(npan, nsplit, s, g));
+    TArgs t;
+    t.A = A;
+    t.lda = lda;
+    t.up = up;
+    t.c0 = 0;
+    t.bw = (int)std::min<int64_t>(pl.n, (int64_t)npan * NB);
+    t.wpart = w.wpart2;
+    t.nsplit = nsplit;
+    t.nxpad = NB;
+    t.wstride = (size_t)nsplit * NB * NB;
+    t.T = w.wp2;
+    HQR_CK(k_tfactor(npan, s, t));
+    return 0;
+}
+
+// The panels applied to at most SN_COLS columns, one launch per panel and one
+// more (stored_step_kernel): each launch finishes the panel before and forms
+// V^T B of its own.  The parts' X live in w.gpart: two buffers of at most
+// ceil(m / 64) parts of 64 x 16, which is half of its ceil(m / 64) blocks of
+// 64 x 64.  At most 128 parts, since every workgroup sums all of them.
+static int stored_steps(const Plan &pl, const Work &w, const double *T, const double *A, int64_t lda,
+                        const double *up, double *B, int64_t ldb, int nrhs, bool transpose, int npan, hipStream_t s)
+{
+    const int tiles = (int)((pl.m + 64 * 128 - 1) / (64 * 128));
+    const size_t half = (size_t)pl.ngroups * NB * SN_COLS;
+    StoredStepArgs a;
+    a.A = A;
+    a.lda = lda;
+    a.up = up;
+    a.B = B;
+    a.ldb = ldb;
+    a.m = pl.m;
+    a.nrhs = nrhs;
+    a.tiles = tiles;
+    a.tmode = transpose ? 0 : 1;
+    int prev = -1, parts_prev = 0;
+    for (int q = 0; q <= npan; ++q) {
+        const int cur = (q < npan) ? (transpose ? q : npan - 1 - q) : -1;
+        auto width = [&](int p) { return (p < 0) ? 0 : (int)std::min<int64_t>(NB, pl.n - (int64_t)p * NB); };
+        a.cp = std::max(prev, 0) * NB;
+        a.bwp = width(prev);
+        a.c0 = std::max(cur, 0) * NB;
+        a.bw = width(cur);
+        a.base = (prev < 0) ? a.c0 : (cur < 0) ? a.cp : std::min(a.cp, a.c0);
+        a.T = T + (size_t)a.cp * NB;
+        a.xin = w.gpart + (size_t)(q & 1) * half;
+        a.nparts = parts_prev;
+        a.xout = w.gpart + (size_t)((q + 1) & 1) * half;
+        parts_prev = (int)((pl.m - a.base + 64 * tiles - 1) / (64 * tiles));
+        HQR_CK(k_stored_step(parts_prev, s, a));
+        prev = cur;
+    }
+    return 0;
+}
+
 // B <- Q^T B (transpose) or Q B with the stored reflectors in (A, up).  With
 // skip, B's column j is only touched by the panels that start at or before
 // column j: B then starts as leading columns of the identity, and no
@@ -949,16 +1017,20 @@ static int apply_stored(const Plan &pl, const Work &w, const double *A, int64_t 
         const WgDesc d{m, n, nrhs, lda, ldb, const_cast<double *>(A), B, const_cast<double *>(up), nullptr, 0, fl};
         return launch_wg_single(v, d, nullptr, s);
     }
-    const int npan = (int)((n + NB - 1) / NB);
+    int npan = (int)((n + NB - 1) / NB);
+    if (skip) npan = (int)std::min<int64_t>(npan, (nrhs + NB - 1) / NB);   // later panels meet no column
+    const double *T = w.wp2;
+    int rc = stored_t(pl, w, A, lda, up, npan, s);
+    if (rc) return rc;
+    if (nrhs <= SN_COLS) return stored_steps(pl, w, T, A, lda, up, B, ldb, (int)nrhs, transpose, npan, s);
     for (int q = 0; q < npan; ++q) {
         const int p = transpose ? q : npan - 1 - q;
         const int64_t c0 = (int64_t)p * NB;
         const int bw = (int)std::min<int64_t>(NB, n - c0);
         const int64_t j0 = skip ? c0 : 0;
-        if (nrhs <= j0) continue;
-        int rc = apply_panel_block(pl, TrailBufs{w.wpart, w.T, w.wp}, const_cast<double *>(A), lda,
-                                   B + (size_t)j0 * ldb, ldb, up, (int)c0, bw, 0, 0, (int)(nrhs - j0), false, s,
-                                   false, 0, nullptr, 0, !transpose);
+        rc = apply_panel_block(pl, TrailBufs{w.wpart, const_cast<double *>(T) + (size_t)p * NB * NB, w.wp},
+                               const_cast<double *>(A), lda, B + (size_t)j0 * ldb, ldb, up, (int)c0, bw, 0, 0,
+                               (int)(nrhs - j0), true, s, false, 0, nullptr, 0, !transpose);
         if (rc) return rc;
     }
     return 0;

@@ -41,9 +41,9 @@ hipError_t k_narrow_vtx(dim3 grid, hipStream_t s, const NarrowArgs &a)
     return hipGetLastError();
 }
 
-hipError_t k_tfactor(hipStream_t s, const TArgs &a)
+hipError_t k_tfactor(int panels, hipStream_t s, const TArgs &a)
 {
-    HQR_LAUNCH(K_TFACTOR, tfactor_kernel, dim3(1), dim3(256), 0, s, a);
+    HQR_LAUNCH(K_TFACTOR, tfactor_kernel, dim3(panels), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
