@@ -34,7 +34,7 @@ import numpy as np
 
 M_BUCKETS = [(1, 64), (65, 128), (129, 256), (257, 512), (513, 1024)]
 N_BUCKETS = [(1, 16), (17, 32), (33, 64), (65, 128), (129, 256), (257, 512), (513, 1024)]
-BATCH_M_BUCKETS = [(1, 256), (257, 512), (513, 1024)]
+BATCH_M_BUCKETS = [(1, 256)]   # larger instances take the 512-thread kernel
 OCCUPANCIES = (1, 2, 3, 4)
 LDS_BYTES = 160 * 1024
 

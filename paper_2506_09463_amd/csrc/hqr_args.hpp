@@ -473,6 +473,9 @@ const WgVariant *wg_variants(int *count);
 hipError_t k_wg_single(const WgVariant *v, hipStream_t s, const WgDesc &d, int *info);
 hipError_t k_wg_batched(const WgVariant *v, int grid, hipStream_t s, const WgDesc *desc, int count, int *head,
                         int *info);
+// instances of 257 .. 1024 rows (all to factor, or all stored), 512 threads,
+// one workgroup per CU
+hipError_t k_wg_batched_rows(bool factor, int grid, hipStream_t s, const WgDesc *desc, int count, int *head, int *info);
 
 // hqr_tsqr.hpp (k_tsqr.hip)
 hipError_t k_tsqr_desc(hipStream_t s, const TsqrArgs &a);

@@ -143,7 +143,11 @@ static const WgVariant *pick_wg_batched(int64_t mmax, int64_t nmax)
     if (c >= 0 && c < cnt && batch_variant(v[c]) && v[c].max_rows >= mmax) return &v[c];
     const WgVariant *best = nullptr;
     for (int i = 0; i < cnt; ++i)
-        if (batch_variant(v[i]) && v[i].max_rows >= mmax && (!best || v[i].max_rows < best->max_rows)) best = &v[i];
+        // equal rows: the deepest loads (1024 rows: 7.8 ms for 8 blocks
+        // together, 8.3 for one, on 512 uneven instances)
+        if (batch_variant(v[i]) && v[i].max_rows >= mmax &&
+            (!best || v[i].max_rows < best->max_rows || (v[i].max_rows == best->max_rows && v[i].pipe > best->pipe)))
+            best = &v[i];
     return best;
 }
 
@@ -1259,10 +1263,15 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
         cost[i] = 2.0 * mm * nn * nn - 2.0 / 3.0 * nn * nn * nn + 4.0 * mm * nn * (double)nrhs[i] + mm;
         max_ntot = std::max<int>(max_ntot, (int)(n[i] + nrhs[i]));
     }
-    // The one-workgroup blocked kernel takes every instance the chosen variant
-    // holds; the rest (more rows, or n * nrhs beyond its staging area) go to
-    // the streaming kernel in a second launch.  Each group runs longest
-    // first; ties keep caller order, so the order depends on shapes only.
+    // Four groups, each a launch of its own: instances above BATCH_NT rows
+    // (3: to factor, 2: stored) take 512 threads, whose update by rows keeps twice the bytes in
+    // flight and reads the trailing columns once per panel; smaller ones (1)
+    // a 256-thread variant, where a panel's steps, not its update, take the
+    // time; and what neither holds (0: more rows, or n * nrhs beyond the
+    // staging area) the streaming kernel.  The line depends on an instance's
+    // own rows only.  A tuning rule for the batch's largest instance puts the
+    // first three into one launch of the variant it names.  Each group runs
+    // longest first; ties keep caller order.
     std::vector<char> fits((size_t)count);
     int64_t mmax = 0, nmax = 0;
     for (int i = 0; i < count; ++i) {
@@ -1272,6 +1281,18 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
             nmax = std::max(nmax, n[i]);
         }
     }
+    if (mmax > BATCH_NT && tune_lookup(HQR_TUNE_BATCHED, mmax, nmax, HQR_PREC_FP64) < 0) {
+        mmax = nmax = 0;
+        for (int i = 0; i < count; ++i) {
+            if (!fits[i]) continue;
+            if (m[i] > BATCH_NT) {
+                fits[i] = (factored && factored[i]) ? 2 : 3;
+            } else {
+                mmax = std::max(mmax, m[i]);
+                nmax = std::max(nmax, n[i]);
+            }
+        }
+    }
     const WgVariant *var = pick_wg_batched(mmax, nmax);
     std::vector<int> order((size_t)count);
     std::iota(order.begin(), order.end(), 0);
@@ -1279,7 +1300,11 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
         if (fits[a] != fits[b]) return fits[a] > fits[b];
         return cost[a] > cost[b];
     });
-    int nwg = 0;
+    int nfac = 0;
+    while (nfac < count && fits[order[nfac]] == 3) ++nfac;
+    int nrow = nfac;
+    while (nrow < count && fits[order[nrow]] == 2) ++nrow;
+    int nwg = nrow;
     while (nwg < count && fits[order[nwg]]) ++nwg;
     std::vector<BatchDesc> sorted((size_t)count);
     for (int i = 0; i < count; ++i) sorted[i] = d[order[i]];
@@ -1309,13 +1334,32 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
     memcpy(img.data() + sizeof(WgDesc) * (size_t)nwg, sorted.data() + nwg, sizeof(BatchDesc) * (size_t)(count - nwg));
     int rc = stage_upload(img.data(), img.size(), dbase, stream);
     if (rc) return rc;
-    HQR_CK(k_fill_int(stream, head, 0, (int64_t)2));
+    HQR_CK(k_fill_int(stream, head, 0, (int64_t)4));
     HQR_CK(hipGetLastError());
-    if (nwg > 0) {
+    // the one-workgroup groups side by side: the others fill the CUs that the
+    // longest factorizations leave (in one stream they would wait for the
+    // last of them)
+    hipStream_t s_rest = stream;
+    StreamCtx *ctx = nullptr;
+    if (nfac > 0 && nfac < nwg && (ctx = stream_ctx(stream)) != nullptr) {
+        HQR_CK(hipEventRecord(ctx->ev[3], stream));
+        HQR_CK(hipStreamWaitEvent(ctx->side, ctx->ev[3], 0));
+        s_rest = ctx->side;
+    }
+    const WgDesc *wd = (const WgDesc *)dbase;
+    if (nfac > 0) HQR_CK(k_wg_batched_rows(true, std::min(nfac, num_cus()), stream, wd, nfac, head + 2, info));
+    if (nrow > nfac)
+        HQR_CK(k_wg_batched_rows(false, std::min(nrow - nfac, num_cus()), s_rest, wd + nfac, nrow - nfac, head + 3,
+                                 info));
+    if (nwg > nrow) {
         int occ = tune_lookup(HQR_TUNE_OCCUPANCY, mmax, nmax, HQR_PREC_FP64);
         occ = (occ >= 1) ? std::min(occ, var->per_cu) : std::min(var->per_cu, 2);
-        const int grid = std::min(nwg, occ * num_cus());
-        HQR_CK(k_wg_batched(var, grid, stream, (const WgDesc *)dbase, nwg, head, info));
+        const int grid = std::min(nwg - nrow, occ * num_cus());
+        HQR_CK(k_wg_batched(var, grid, s_rest, wd + nrow, nwg - nrow, head, info));
+    }
+    if (ctx) {
+        HQR_CK(hipEventRecord(ctx->ev[2], ctx->side));
+        HQR_CK(hipStreamWaitEvent(stream, ctx->ev[2], 0));
     }
     if (nwg < count) {
         BatchArgs a;

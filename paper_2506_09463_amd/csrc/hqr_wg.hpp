@@ -30,20 +30,53 @@ namespace hqr {
 
 // Rows a variant holds (NT threads x QM rows) bound m; n * nrhs must fit the
 // V area for the back-substitution.
+//
+// V's rows are WG_LD = 17 doubles apart.  With 512 threads (WG_ROWS_NT) the
+// trailing update also needs the waves' partial W in LDS; 1024 rows of 17
+// doubles leave no room for them, so these rows are 16 doubles: row r of a
+// 16-row block at place 4 (r % 4) + (r % 16) / 4 of it, its columns XORed with
+// that place, so that the reads of both products of the update take every
+// bank once (rows of 16 doubles alone would meet in 2 to 16 ways).
+constexpr int WG_ROWS_NT = 512;
+
 template <int NT, int QM>
 struct WgShared {
-    double v[NT * QM * WG_LD];
+    static constexpr bool SWZ = NT >= WG_ROWS_NT && QM > 1;
+    static constexpr int LD = SWZ ? WG_P : WG_LD;
+    static constexpr bool ROWS = NT >= WG_ROWS_NT;   // trailing update split by rows
+    static constexpr int G = (QM > 1) ? 1 : 2;       // its 16-column tiles at a time
+    double v[NT * QM * LD];
     double t[WG_P * WG_LD];
     double red[2][NT / 64][WG_P + 1];
     double prow[2][WG_P];
     double aux[NT / 64];
     int isc[4];
+    double wpart[ROWS ? NT / 64 * G * WG_P * WG_P : 1];
+
+    __device__ __forceinline__ static int vi(int r, int c)
+    {
+        if (!SWZ) return r * WG_LD + c;
+        const int p = ((r & 3) << 2) | ((r >> 2) & 3);
+        return ((r & ~15) | p) * WG_P + (c ^ p);
+    }
 };
 
 template <int NT, int QM>
 constexpr int64_t wg_max_rows() { return (int64_t)NT * QM; }
 template <int NT, int QM>
-constexpr int64_t wg_max_x() { return (int64_t)NT * QM * WG_LD; }
+constexpr int64_t wg_max_x() { return (int64_t)NT * QM * WgShared<NT, QM>::LD; }
+
+// The thread's index.  With 512 threads (256 registers a wave) it is opaque at
+// each use: LDS addresses formed from it are then not hoisted out of the panel
+// loop, where the register limit would spill them and every panel step wait
+// for their reloads from memory.
+template <int NT>
+HQR_DEV int wg_tid()
+{
+    int t = (int)threadIdx.x;
+    if constexpr (NT >= WG_ROWS_NT) asm volatile("" : "+v"(t));
+    return t;
+}
 
 // Cross-lane moves of a double without LDS: gfx950's permlane swaps between
 // the wave's halves (32) and between row pairs (16), and DPP within rows.
@@ -184,7 +217,7 @@ HQR_DEV double row_bcast16(double v, int i)
 template <int NT, int QM>
 HQR_DEV double wg_block_reduce(double x, int op, WgShared<NT, QM> &sh)
 {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const double y = __shfl_xor(x, o);
@@ -259,7 +292,7 @@ HQR_DEV void wg_panel_step(const WgDesc &d, int c0, int pw, int m, double (&a)[Q
                            WgShared<NT, QM> &sh)
 {
     constexpr int NWV = NT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
     if (k >= pw) return;
     const int pr = c0 + k;
     const int buf = k & 1;
@@ -377,44 +410,32 @@ HQR_DEV void wg_panel_steps(const WgDesc &d, int c0, int pw, int m, double (&a)[
     (wg_panel_step<NT, QM, Ks>(d, c0, pw, m, a, myup, sh), ...);
 }
 
-// T of a factored panel: the Gram matrix G = V^T V of the panel's vectors
-// (in sh.v, rows 0 .. nrows-1; columns beyond pw zero) on MFMA, then T row i
-// by thread i from T[i][k] = -tau_k sum_{l=i}^{k-1} T[i][l] G[l][k], with
-// tau_k = T[k][k] as the column steps left it.  Starts after a barrier, ends
-// with one.
+// sh.t = the sum over the waves of their 16 x 16 partials (D layout), in wave
+// order.  Ends with a barrier.
 template <int NT, int QM>
-HQR_DEV void wg_panel_t(int nrows, int pw, WgShared<NT, QM> &sh)
+HQR_DEV void wg_sum_parts(f64x4 g, WgShared<NT, QM> &sh)
 {
     constexpr int NWV = NT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    double tau[WG_P];
-    if (tid < WG_P) {
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
 #pragma unroll
-        for (int k = 0; k < WG_P; ++k) tau[k] = sh.t[k * WG_LD + k];
-    }
-    f64x4 g = {0.0, 0.0, 0.0, 0.0};
-    const int i16 = lane & 15, kq = lane >> 4;
-    const int nb16 = (nrows + 15) / 16;
-    for (int rb = w; rb < nb16; rb += NWV) {
+    for (int r4 = 0; r4 < 4; ++r4) sh.wpart[(w * 4 + r4) * 64 + lane] = g[r4];
+    __syncthreads();
+    if (tid < 256) {
+        double s = 0.0;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int rr = rb * 16 + 4 * kq + s;
-            const double vv = (rr < nrows) ? sh.v[rr * WG_LD + i16] : 0.0;
-            g = __builtin_amdgcn_mfma_f64_16x16x4f64(vv, vv, g, 0, 0, 0);
-        }
+        for (int i = 0; i < NWV; ++i) s += sh.wpart[i * 256 + tid];
+        // element tid = 64 r4 + 16 k + j is G[4 r4 + k][j]
+        sh.t[(tid >> 4) * WG_LD + (tid & 15)] = s;
     }
-    __syncthreads();   // the taus are in registers before G overwrites the T area
-    // G[i][j] at lane j + 16 (i % 4), reg i / 4; waves add into sh.t in turn
-    for (int wv = 0; wv < NWV; ++wv) {
-        if (w == wv) {
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                double *dst = &sh.t[(4 * r4 + kq) * WG_LD + i16];
-                *dst = (wv == 0) ? g[r4] : *dst + g[r4];
-            }
-        }
-        __syncthreads();
-    }
+    __syncthreads();
+}
+
+// T from G = V^T V in sh.t, in place, row i by thread i < 16 (tau: the
+// panel's -1/b_k).  Ends with a barrier.
+template <int NT, int QM>
+HQR_DEV void wg_t_rows(const double (&tau)[WG_P], int pw, WgShared<NT, QM> &sh)
+{
+    const int tid = wg_tid<NT>();
     // right-looking: once T[i][l] is final it is added into the sums of all
     // later columns (the same terms in the same order as summing each column
     // over l = i .. k-1 in turn, with the sums no longer one long chain)
@@ -440,13 +461,57 @@ HQR_DEV void wg_panel_t(int nrows, int pw, WgShared<NT, QM> &sh)
     __syncthreads();
 }
 
+// T of a factored panel: the Gram matrix G = V^T V of the panel's vectors
+// (in sh.v, rows 0 .. nrows-1; columns beyond pw zero) on MFMA, then T row i
+// by thread i from T[i][k] = -tau_k sum_{l=i}^{k-1} T[i][l] G[l][k], with
+// tau_k = T[k][k] as the column steps left it.  Starts after a barrier, ends
+// with one.
+template <int NT, int QM>
+HQR_DEV void wg_panel_t(int nrows, int pw, WgShared<NT, QM> &sh)
+{
+    constexpr int NWV = NT / 64;
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
+    double tau[WG_P];
+    if (tid < WG_P) {
+#pragma unroll
+        for (int k = 0; k < WG_P; ++k) tau[k] = sh.t[k * WG_LD + k];
+    }
+    f64x4 g = {0.0, 0.0, 0.0, 0.0};
+    const int i16 = lane & 15, kq = lane >> 4;
+    const int nb16 = (nrows + 15) / 16;
+    for (int rb = w; rb < nb16; rb += NWV) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int rr = rb * 16 + 4 * kq + s;
+            const double vv = (rr < nrows) ? sh.v[sh.vi(rr, i16)] : 0.0;
+            g = __builtin_amdgcn_mfma_f64_16x16x4f64(vv, vv, g, 0, 0, 0);
+        }
+    }
+    __syncthreads();   // the taus are in registers before G overwrites the T area
+    // G[i][j] at lane j + 16 (i % 4), reg i / 4; waves add into sh.t in turn
+    // (or all leave their partials for one sum)
+    if constexpr (WgShared<NT, QM>::ROWS) wg_sum_parts<NT, QM>(g, sh);
+    else
+    for (int wv = 0; wv < NWV; ++wv) {
+        if (w == wv) {
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                double *dst = &sh.t[(4 * r4 + kq) * WG_LD + i16];
+                *dst = (wv == 0) ? g[r4] : *dst + g[r4];
+            }
+        }
+        __syncthreads();
+    }
+    wg_t_rows<NT, QM>(tau, pw, sh);
+}
+
 // Factor columns c0 .. c0+pw-1 (rows c0 .. m-1) in registers; write them
 // back, leave V (rows relative to c0, up on the diagonal, zeros above) and T
 // in LDS.  Ends with a barrier.
 template <int NT, int QM>
 HQR_DEV void wg_panel_factor(const WgDesc &d, int c0, int pw, WgShared<NT, QM> &sh)
 {
-    const int tid = threadIdx.x;
+    const int tid = wg_tid<NT>();
     const int m = (int)d.m, nrows = m - c0;
     const size_t lda = (size_t)d.lda;
     double *const Ap = d.A + (size_t)c0 * lda + c0;   // A[c0][c0]
@@ -479,9 +544,9 @@ HQR_DEV void wg_panel_factor(const WgDesc &d, int c0, int pw, WgShared<NT, QM> &
         for (int j = 0; j < WG_P; ++j) {
             if (j < pw) {
                 const double *col = Ap + (size_t)j * lda;
-                for (int rr = tid; rr < nrows; rr += NT) sh.v[rr * WG_LD + j] = col[rr];
+                for (int rr = tid; rr < nrows; rr += NT) sh.v[sh.vi(rr, j)] = col[rr];
             } else {
-                for (int rr = tid; rr < nrows; rr += NT) sh.v[rr * WG_LD + j] = 0.0;
+                for (int rr = tid; rr < nrows; rr += NT) sh.v[sh.vi(rr, j)] = 0.0;
             }
         }
         if (tid < WG_P) {
@@ -493,7 +558,7 @@ HQR_DEV void wg_panel_factor(const WgDesc &d, int c0, int pw, WgShared<NT, QM> &
         for (int q = 0; q < QM; ++q) {
             const int rr = tid + NT * q;
 #pragma unroll
-            for (int j = 0; j < WG_P; ++j) a[q][j] = (rr < nrows) ? sh.v[rr * WG_LD + j] : 0.0;
+            for (int j = 0; j < WG_P; ++j) a[q][j] = (rr < nrows) ? sh.v[sh.vi(rr, j)] : 0.0;
         }
     }
     // up of the reflector whose pivot row this thread owns (V's diagonal);
@@ -505,15 +570,20 @@ HQR_DEV void wg_panel_factor(const WgDesc &d, int c0, int pw, WgShared<NT, QM> &
         // the factored panel from registers to A; V (up on the diagonal, zeros
         // above it) into LDS for the trailing update.  The diagonal of row
         // rr < 16 belongs to thread rr (q = 0), whose myup it is.
+        const int to = wg_tid<NT>();
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
-            const int rr = tid + NT * q;
+            const int rr = to + NT * q;
             if (rr < nrows) {
 #pragma unroll
                 for (int j = 0; j < WG_P; ++j) {
                     Ap[(size_t)j * lda + rr] = a[q][j];
-                    sh.v[rr * WG_LD + j] = (rr < j) ? 0.0 : ((rr == j) ? myup : a[q][j]);
+                    sh.v[sh.vi(rr, j)] = (rr < j) ? 0.0 : ((rr == j) ? myup : a[q][j]);
                 }
+            } else if (WgShared<NT, QM>::ROWS && rr < ((nrows + 15) & ~15)) {
+                // the update by rows reads whole 16-row blocks
+#pragma unroll
+                for (int j = 0; j < WG_P; ++j) sh.v[sh.vi(rr, j)] = 0.0;
             }
         }
         __syncthreads();
@@ -525,27 +595,27 @@ HQR_DEV void wg_panel_factor(const WgDesc &d, int c0, int pw, WgShared<NT, QM> &
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
         const int rr = tid + NT * q;
-        if (rr < nrows) {
+        if (rr < nrows || (WgShared<NT, QM>::ROWS && rr < ((nrows + 15) & ~15))) {
 #pragma unroll
-            for (int j = 0; j < WG_P; ++j) sh.v[rr * WG_LD + j] = a[q][j];
+            for (int j = 0; j < WG_P; ++j) sh.v[sh.vi(rr, j)] = a[q][j];   // zeros past nrows
         }
     }
     __syncthreads();
 #pragma unroll 1
     for (int j = 0; j < pw; ++j) {
         double *col = Ap + (size_t)j * lda;
-        for (int rr = tid; rr < nrows; rr += NT) col[rr] = sh.v[rr * WG_LD + j];
+        for (int rr = tid; rr < nrows; rr += NT) col[rr] = sh.v[sh.vi(rr, j)];
     }
     __syncthreads();
     if (tid < WG_P && tid < nrows) {
 #pragma unroll
         for (int j = 0; j < WG_P; ++j) {
-            if (j >= tid) sh.v[tid * WG_LD + j] = (j == tid) ? myup : 0.0;
+            if (j >= tid) sh.v[sh.vi(tid, j)] = (j == tid) ? myup : 0.0;
         }
     }
 #pragma unroll 1
     for (int j = pw; j < WG_P; ++j)
-        for (int rr = tid; rr < nrows; rr += NT) sh.v[rr * WG_LD + j] = 0.0;
+        for (int rr = tid; rr < nrows; rr += NT) sh.v[sh.vi(rr, j)] = 0.0;
     __syncthreads();
     wg_panel_t<NT, QM>(nrows, pw, sh);
 }
@@ -556,9 +626,32 @@ template <int NT, int QM>
 __device__ __noinline__ void wg_panel_load(const WgDesc &d, int64_t c0, int pw, WgShared<NT, QM> &sh)
 {
     constexpr int NWV = NT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
     const int64_t m = d.m;
     const int64_t nrows = m - c0;
+    if constexpr (WgShared<NT, QM>::ROWS) {
+        // every load in flight before the first is used: rows and columns
+        // clamped into the panel, what lies outside V replaced by selects (a
+        // load behind its own branch is waited for there: 16 a row)
+        double a[QM][WG_P], u[QM];
+#pragma unroll
+        for (int q = 0; q < QM; ++q) {
+            const int rr = tid + NT * q, rc = min(rr, (int)nrows - 1);
+            const double *src = d.A + (size_t)c0 * d.lda + c0 + rc;
+#pragma unroll
+            for (int j = 0; j < WG_P; ++j) a[q][j] = src[(size_t)min(j, pw - 1) * d.lda];
+            u[q] = d.up[c0 + min(rr, pw - 1)];
+        }
+#pragma unroll
+        for (int q = 0; q < QM; ++q) {
+            const int rr = tid + NT * q;
+#pragma unroll
+            for (int j = 0; j < WG_P; ++j) {
+                const double v = (rr > j) ? a[q][j] : ((rr == j) ? u[q] : 0.0);
+                sh.v[sh.vi(rr, j)] = (rr < (int)nrows && j < pw) ? v : 0.0;
+            }
+        }
+    } else
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
         const int64_t rr = tid + (int64_t)NT * q;
@@ -569,7 +662,7 @@ __device__ __noinline__ void wg_panel_load(const WgDesc &d, int64_t c0, int pw, 
                 if (rr > j) v = d.A[(size_t)(c0 + j) * d.lda + c0 + rr];
                 else if (rr == j) v = d.up[c0 + j];
             }
-            sh.v[rr * WG_LD + j] = v;
+            sh.v[sh.vi((int)rr, j)] = v;
         }
     }
     __syncthreads();
@@ -582,11 +675,14 @@ __device__ __noinline__ void wg_panel_load(const WgDesc &d, int64_t c0, int pw, 
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const int64_t rr = rb * 16 + 4 * kq + s;
-            const double vv = sh.v[rr * WG_LD + i16];
+            const double vv = sh.v[sh.vi((int)rr, i16)];
             g = __builtin_amdgcn_mfma_f64_16x16x4f64(vv, vv, g, 0, 0, 0);
         }
     }
     // G[i][j] at lane j + 16 (i % 4), reg i / 4; waves add into sh.t in turn
+    // (or all leave their partials for one sum)
+    if constexpr (WgShared<NT, QM>::ROWS) wg_sum_parts<NT, QM>(g, sh);
+    else
     for (int wv = 0; wv < NWV; ++wv) {
         if (w == wv) {
 #pragma unroll
@@ -597,6 +693,19 @@ __device__ __noinline__ void wg_panel_load(const WgDesc &d, int64_t c0, int pw, 
             }
         }
         __syncthreads();
+    }
+    if constexpr (WgShared<NT, QM>::ROWS) {
+        double tau[WG_P];
+        if (tid < WG_P) {
+#pragma unroll
+            for (int k = 0; k < WG_P; ++k) {
+                const int64_t c = c0 + min(k, pw - 1);
+                const double upk = d.up[c], rkk = d.A[(size_t)c * d.lda + c];
+                tau[k] = (upk != 0.0) ? -1.0 / (upk * rkk) : 0.0;
+            }
+        }
+        wg_t_rows<NT, QM>(tau, pw, sh);
+        return;
     }
     // T row i by thread i (T upper): T[i][k] = -tau_k sum_{l=i}^{k-1} T[i][l] G[l][k]
     double trow[WG_P];
@@ -641,7 +750,7 @@ template <int NT, int QM, int PIPE, bool QMODE = false>
 HQR_DEV void wg_trailing(const WgDesc &d, int64_t c0, int64_t colA, int64_t ncA, WgShared<NT, QM> &sh)
 {
     constexpr int NWV = NT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
     const int i16 = lane & 15, kq = lane >> 4;
     const int64_t nrows = d.m - c0;
     const int64_t ntot = ncA + d.nrhs;
@@ -667,7 +776,7 @@ HQR_DEV void wg_trailing(const WgDesc &d, int64_t c0, int64_t colA, int64_t ncA,
                 const int64_t rr0 = (rb0 + u) * 16 + 4 * kq;
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    const double av = (rr0 + s < nrows) ? sh.v[(rr0 + s) * WG_LD + i16] : 0.0;
+                    const double av = (rr0 + s < nrows) ? sh.v[sh.vi((int)rr0 + s, i16)] : 0.0;
                     acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, cv[u][s], acc[s], 0, 0, 0);
                 }
             }
@@ -700,7 +809,7 @@ HQR_DEV void wg_trailing(const WgDesc &d, int64_t c0, int64_t colA, int64_t ncA,
                 const int64_t rr = (rb0 + u) * 16 + i16;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const double bv = (rr < nrows) ? sh.v[rr * WG_LD + 4 * q + kq] : 0.0;
+                    const double bv = (rr < nrows) ? sh.v[sh.vi((int)rr, 4 * q + kq)] : 0.0;
                     cacc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-wp[q], bv, cacc[u], 0, 0, 0);
                 }
 #pragma unroll
@@ -711,12 +820,199 @@ HQR_DEV void wg_trailing(const WgDesc &d, int64_t c0, int64_t colA, int64_t ncA,
     }
 }
 
+// The same update with the rows split over the waves (512 threads): wave w
+// takes 16-row blocks w, w + 8, .. of G 16-column tiles at a time and keeps
+// their C in registers from V^T C to C - V W', so C is read once and written
+// once per panel (the form above reads it twice) and all waves work on a
+// short column list.  The waves' partial W are summed through LDS in wave
+// order; the next tiles' C is loaded before that.  The row order within a
+// block makes one register layout serve both products: register s of lane
+// (j, kq) is row 4 kq + s of column j, the B operand of V^T C's s-th k-chunk
+// and, with V's rows in the order 4 (i % 4) + i / 4, the accumulator of
+// C - V W'.  V's rows up to the next multiple of 16 must be in LDS (zeros past
+// the last row); columns and rows outside are loaded clamped and not stored.
+//
+//
+// Bound: bytes in flight from one CU, then its MFMA rate.  NU block rounds
+// (8 NU blocks, those past the last masked) are straight code: a branch per
+// block made every load, LDS read and MFMA wait for the one before it.
+// 2000 instances (n <= 512, m <= 1024, 8 columns) took
+// 18.5 ms with 256 threads and the form above, 15.5 ms so; one 800 x 400
+// instance alone 4.1 and 3.3 ms (about 6.7 us per tile, 3 of them MFMA).
+template <int NT, int QM, bool QMODE, int NU>
+HQR_DEV void wg_trailing_rows(const WgDesc &d, int c0, int64_t colA, int64_t ncA, WgShared<NT, QM> &sh)
+{
+    constexpr int NWV = NT / 64, G = WgShared<NT, QM>::G;
+    // global-space pointers: a flat load (the matrices' addresses come from
+    // memory) also counts as an LDS access, so the reads of V and W would
+    // wait for the next tiles' loads
+    typedef __attribute__((address_space(1))) double gdouble;
+    const int tid = wg_tid<NT>();
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i16 = lane & 15, kq = lane >> 4;
+    const int nrows = (int)d.m - c0;
+    const int64_t ntot = ncA + d.nrhs;
+    const int ngrp = (int)((ntot + 16 * G - 1) / (16 * G));
+    const int nb16 = (nrows + 15) / 16;
+    const int vrow = 4 * (i16 & 3) + (i16 >> 2);
+    gdouble *const Ab = (gdouble *)(d.A + (size_t)colA * d.lda + c0);
+    gdouble *const Bb = (gdouble *)(d.B + c0);
+    const int64_t lda = d.lda, ldb = d.ldb;
+    // this lane's column of tile g of group grp (clamped to the last column)
+    auto col = [&](int grp, int g) {
+        const int64_t ci = min<int64_t>((int64_t)(grp * G + g) * 16 + i16, ntot - 1);
+        return (ci < ncA) ? Ab + ci * lda : Bb + (ci - ncA) * ldb;
+    };
+    // Four rows from one address per block: the first row clamped to
+    // nrows - 4 (nrows >= 16), so the last block's lanes may hold rows above
+    // their own; tail() puts the rows they share with it in place.  What lies
+    // past the last row is another row of the same column, which V's zeros
+    // take out.
+    auto load4 = [&](const gdouble *cp, int u, f64x4 &c) {
+        const gdouble *q = cp + min(16 * (w + NWV * u) + 4 * kq, nrows - 4);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) c[s] = q[s];
+    };
+    auto tail = [&](f64x4 (&c)[G][NU]) {
+        if ((nrows & 3) == 0) return;
+        const int tb = nb16 - 1, r0 = 16 * tb + 4 * kq, sh4 = r0 - (nrows - 4);   // 1 .. 3: shift down
+        const bool part = sh4 >= 1 && sh4 <= 3;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            if (w + NWV * u != tb) continue;
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) {
+                    double x = c[g][u][s];
+#pragma unroll
+                    for (int e = s + 1; e < 4; ++e) x = (part && sh4 == e - s) ? c[g][u][e] : x;
+                    c[g][u][s] = x;
+                }
+        }
+    };
+    // V's LDS addresses: block u is a constant step from block 0
+    const double *vw[4], *vu[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        vw[s] = &sh.v[sh.vi(16 * w + 4 * kq + s, i16)];
+        vu[s] = &sh.v[sh.vi(16 * w + vrow, 4 * s + kq)];
+    }
+    constexpr int VSTEP = 16 * NWV * WgShared<NT, QM>::LD;
+    auto group = [&](int grp, f64x4 (&cur)[G][NU], f64x4 (&nxt)[G][NU]) {
+        tail(cur);
+        f64x4 wacc[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) wacc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const bool in = w + NWV * u < nb16;   // else stale LDS
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                double av = vw[s][VSTEP * u];
+                av = in ? av : 0.0;
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    wacc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, cur[g][u][s], wacc[g], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) sh.wpart[((w * G + g) * 4 + r4) * 64 + lane] = wacc[g][r4];
+        __syncthreads();
+        f64x4 wp[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            f64x4 wm;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                double x = sh.wpart[(g * 4 + r4) * 64 + lane];
+#pragma unroll
+                for (int i = 1; i < NWV; ++i) x += sh.wpart[((i * G + g) * 4 + r4) * 64 + lane];
+                wm[r4] = x;
+            }
+            wp[g] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double tv = QMODE ? sh.t[i16 * WG_LD + 4 * q + kq] : sh.t[(4 * q + kq) * WG_LD + i16];
+                wp[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, wm[q], wp[g], 0, 0, 0);
+            }
+        }
+        __syncthreads();   // before the next tiles' partials
+        // The next tiles' loads go out between the products (issued together
+        // they keep the address unit busy for as long as the products keep
+        // the matrix cores).  Blocks past the last one are updated too, and
+        // not stored.
+        const gdouble *np[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) np[g] = col(min(grp + 1, ngrp - 1), g);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) load4(np[g], u, nxt[g][u]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double av = -vu[q][VSTEP * u];
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    cur[g][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, wp[g][q], cur[g][u], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            gdouble *cp = col(grp, g) + 4 * kq;
+            if ((int64_t)(grp * G + g) * 16 + i16 < ntot) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    const int rb = w + NWV * u;
+                    gdouble *q = cp + 16 * rb;
+                    if (16 * rb + 16 <= nrows) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) q[s] = cur[g][u][s];
+                    } else if (rb < nb16) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            if (16 * rb + 4 * kq + s < nrows) q[s] = cur[g][u][s];
+                    }
+                }
+            }
+        }
+    };
+    f64x4 ca[G][NU], cb[G][NU];
+    if (ngrp == 0) return;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const gdouble *cp = col(0, g);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) load4(cp, u, ca[g][u]);
+    }
+    for (int grp = 0; grp < ngrp; grp += 2) {
+        group(grp, ca, cb);
+        if (grp + 1 < ngrp) group(grp + 1, cb, ca);
+    }
+}
+
+// the number of 16-row block rounds picks the straight code
+template <int NT, int QM, bool QMODE>
+HQR_DEV void wg_trailing_by_rows(const WgDesc &d, int c0, int64_t colA, int64_t ncA, WgShared<NT, QM> &sh)
+{
+    const int nb16 = ((int)d.m - c0 + 15) / 16, nu = (nb16 + NT / 64 - 1) / (NT / 64);
+    constexpr int S = QM;   // steps of 1 round up to 512 rows, of 2 above
+    if (nb16 == 1) wg_trailing<NT, QM, 2, QMODE>(d, c0, colA, ncA, sh);   // 1 .. 16 rows
+    else if (nu <= S) wg_trailing_rows<NT, QM, QMODE, S>(d, c0, colA, ncA, sh);
+    else if (nu <= 2 * S) wg_trailing_rows<NT, QM, QMODE, 2 * S>(d, c0, colA, ncA, sh);
+    else if (nu <= 3 * S) wg_trailing_rows<NT, QM, QMODE, 3 * S>(d, c0, colA, ncA, sh);
+    else wg_trailing_rows<NT, QM, QMODE, 4 * S>(d, c0, colA, ncA, sh);
+}
+
 // ------------------------------------------------ residual norms, solve
 template <int NT, int QM>
 __device__ __noinline__ void wg_resnorm(const WgDesc &d)
 {
     constexpr int NWV = NT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
     for (int64_t c = w; c < d.nrhs; c += NWV) {
         const double *bc = d.B + (size_t)c * d.ldb;
         double s = 0.0, mx = 0.0;
@@ -753,7 +1049,7 @@ __device__ __noinline__ void wg_resnorm(const WgDesc &d)
 template <int NT, int QM>
 HQR_DEV void wg_backsolve(const WgDesc &d, int *info, WgShared<NT, QM> &sh)
 {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = wg_tid<NT>(), lane = tid & 63, w = tid >> 6;
     const int64_t n = d.n, nrhs = d.nrhs;
     if (tid == 0) sh.isc[0] = 0x7fffffff;
     __syncthreads();
@@ -874,6 +1170,49 @@ __global__ void __launch_bounds__(NT) wg_batched_kernel(const WgDesc *desc, int 
         __syncthreads();
         if (id >= count) break;
         wg_instance<NT, QM, PIPE>(desc[id], info, sh);
+    }
+}
+
+// One instance with 512 threads: factored and solved (FACTOR) or a stored
+// factorization applied and solved.  Two kernels, so that neither holds the
+// other's registers: the factorization has none to spare.
+template <int QM, bool FACTOR>
+HQR_DEV void wg_instance_rows(const WgDesc &d, int *info, WgShared<WG_ROWS_NT, QM> &sh)
+{
+    constexpr int NT = WG_ROWS_NT;
+    const int n = (int)d.n;
+    for (int c0 = 0; c0 < n; c0 += WG_P) {
+        const int pw = min(n - c0, WG_P);
+        if constexpr (FACTOR) wg_panel_factor<NT, QM>(d, c0, pw, sh);
+        else wg_panel_load<NT, QM>(d, c0, pw, sh);
+        wg_trailing_by_rows<NT, QM, false>(d, c0, c0 + pw, FACTOR ? n - c0 - pw : 0, sh);
+        __syncthreads();
+    }
+    if (d.resnorm && d.nrhs > 0) wg_resnorm<NT, QM>(d);
+    wg_backsolve<NT, QM>(d, info, sh);
+    __syncthreads();
+}
+
+// The same queue over instances of 257 .. 1024 rows, with 512 threads: one
+// row per thread up to 512 rows, two above.  Which of the two an instance
+// takes, like the choice of this kernel, depends on its own rows only.
+template <bool FACTOR>
+__global__ void __launch_bounds__(WG_ROWS_NT) wg_batched_rows_kernel(const WgDesc *desc, int count, int *head, int *info)
+{
+    __shared__ union Sh {
+        WgShared<WG_ROWS_NT, 1> one;
+        WgShared<WG_ROWS_NT, 2> two;
+        __device__ Sh() {}
+    } sh;
+    __shared__ int next;
+    for (;;) {
+        if (threadIdx.x == 0) next = atomicAdd(head, 1);
+        __syncthreads();
+        const int id = next;
+        __syncthreads();
+        if (id >= count) break;
+        if (desc[id].m <= WG_ROWS_NT) wg_instance_rows<1, FACTOR>(desc[id], info, sh.one);
+        else wg_instance_rows<2, FACTOR>(desc[id], info, sh.two);
     }
 }
 

@@ -73,4 +73,12 @@ hipError_t k_wg_batched(const WgVariant *v, int grid, hipStream_t s, const WgDes
     return hipGetLastError();
 }
 
+hipError_t k_wg_batched_rows(bool factor, int grid, hipStream_t s, const WgDesc *desc, int count, int *head, int *info)
+{
+    const dim3 b(WG_ROWS_NT);
+    if (factor) HQR_LAUNCH(K_BATCHED, wg_batched_rows_kernel<true>, dim3(grid), b, 0, s, desc, count, head, info);
+    else HQR_LAUNCH(K_BATCHED, wg_batched_rows_kernel<false>, dim3(grid), b, 0, s, desc, count, head, info);
+    return hipGetLastError();
+}
+
 } // namespace hqr
