@@ -470,12 +470,17 @@ struct WgVariant {
     int index;          // position in wg_variants()
 };
 const WgVariant *wg_variants(int *count);
-hipError_t k_wg_single(const WgVariant *v, hipStream_t s, const WgDesc &d, int *info);
+hipError_t k_wg_single(const WgVariant *v, hipStream_t s, const WgDesc &d, int *info, int *iters);
 hipError_t k_wg_batched(const WgVariant *v, int grid, hipStream_t s, const WgDesc *desc, int count, int *head,
                         int *info);
 // instances of 257 .. 1024 rows (all to factor, or all stored), 512 threads,
 // one workgroup per CU
 hipError_t k_wg_batched_rows(bool factor, int grid, hipStream_t s, const WgDesc *desc, int count, int *head, int *info);
+
+// hqr_tiny.hpp (k_tiny.hip): one problem to factor with m <= TINY_ROWS and
+// 1 <= n, n + nrhs <= TINY_COLS
+constexpr int TINY_ROWS = 128, TINY_COLS = 32;
+hipError_t k_wg_tiny(hipStream_t s, const WgDesc &d, int *info, int *iters);
 
 // hqr_tsqr.hpp (k_tsqr.hip)
 hipError_t k_tsqr_desc(hipStream_t s, const TsqrArgs &a);

@@ -516,106 +516,58 @@ HQR_DEV void wg_panel_factor(const WgDesc &d, int c0, int pw, WgShared<NT, QM> &
     const size_t lda = (size_t)d.lda;
     double *const Ap = d.A + (size_t)c0 * lda + c0;   // A[c0][c0]
     double a[QM][WG_P];
-    if (pw == WG_P) {
-        // full panel: each thread loads its rows of the 16 columns straight
-        // into registers; a row's 16 loads (and those of its other rows) are
-        // all in flight before the first is used, instead of one round trip
-        // per column through LDS
+    // each thread loads its rows of the panel's columns straight into
+    // registers; a row's 16 loads (and those of its other rows) are all in
+    // flight before the first is used.  A ragged last panel's missing columns
+    // are its last column again, replaced by zeros
 #pragma unroll
-        for (int q = 0; q < QM; ++q) {
-            const int rr = tid + NT * q;
-            if (rr < nrows) {
+    for (int q = 0; q < QM; ++q) {
+        const int rr = tid + NT * q;
+        if (rr < nrows) {
+            if (pw == WG_P) {
 #pragma unroll
                 for (int j = 0; j < WG_P; ++j) a[q][j] = Ap[(size_t)j * lda + rr];
             } else {
 #pragma unroll
-                for (int j = 0; j < WG_P; ++j) a[q][j] = 0.0;
+                for (int j = 0; j < WG_P; ++j) a[q][j] = Ap[(size_t)min(j, pw - 1) * lda + rr];
+#pragma unroll
+                for (int j = 0; j < WG_P; ++j) a[q][j] = (j < pw) ? a[q][j] : 0.0;
             }
-        }
-        if (tid < WG_P) {
+        } else {
 #pragma unroll
-            for (int j = 0; j < WG_P; ++j) sh.t[tid * WG_LD + j] = 0.0;
-        }
-        __syncthreads();
-    } else {
-        // ragged last panel: staged in LDS (columns beyond pw as zeros), then
-        // each thread takes its rows into registers
-#pragma unroll 1
-        for (int j = 0; j < WG_P; ++j) {
-            if (j < pw) {
-                const double *col = Ap + (size_t)j * lda;
-                for (int rr = tid; rr < nrows; rr += NT) sh.v[sh.vi(rr, j)] = col[rr];
-            } else {
-                for (int rr = tid; rr < nrows; rr += NT) sh.v[sh.vi(rr, j)] = 0.0;
-            }
-        }
-        if (tid < WG_P) {
-#pragma unroll
-            for (int j = 0; j < WG_P; ++j) sh.t[tid * WG_LD + j] = 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < QM; ++q) {
-            const int rr = tid + NT * q;
-#pragma unroll
-            for (int j = 0; j < WG_P; ++j) a[q][j] = (rr < nrows) ? sh.v[sh.vi(rr, j)] : 0.0;
+            for (int j = 0; j < WG_P; ++j) a[q][j] = 0.0;
         }
     }
+    if (tid < WG_P) {
+#pragma unroll
+        for (int j = 0; j < WG_P; ++j) sh.t[tid * WG_LD + j] = 0.0;
+    }
+    __syncthreads();
     // up of the reflector whose pivot row this thread owns (V's diagonal);
     // the steps leave tau_k on T's diagonal
     double myup = 0.0;
     wg_panel_steps<NT, QM>(d, c0, pw, m, a, myup, sh, std::make_integer_sequence<int, WG_P>{});
     if (tid < pw) d.up[c0 + tid] = myup;
-    if (pw == WG_P) {
-        // the factored panel from registers to A; V (up on the diagonal, zeros
-        // above it) into LDS for the trailing update.  The diagonal of row
-        // rr < 16 belongs to thread rr (q = 0), whose myup it is.
-        const int to = wg_tid<NT>();
-#pragma unroll
-        for (int q = 0; q < QM; ++q) {
-            const int rr = to + NT * q;
-            if (rr < nrows) {
-#pragma unroll
-                for (int j = 0; j < WG_P; ++j) {
-                    Ap[(size_t)j * lda + rr] = a[q][j];
-                    sh.v[sh.vi(rr, j)] = (rr < j) ? 0.0 : ((rr == j) ? myup : a[q][j]);
-                }
-            } else if (WgShared<NT, QM>::ROWS && rr < ((nrows + 15) & ~15)) {
-                // the update by rows reads whole 16-row blocks
-#pragma unroll
-                for (int j = 0; j < WG_P; ++j) sh.v[sh.vi(rr, j)] = 0.0;
-            }
-        }
-        __syncthreads();
-        wg_panel_t<NT, QM>(nrows, pw, sh);
-        return;
-    }
-    // back through LDS: the factored panel to A, then V (up on the diagonal,
-    // zeros above it and beyond pw) stays in LDS for the trailing update
+    // the factored panel from registers to A; V (up on the diagonal, zeros
+    // above it and beyond pw) into LDS for the trailing update.  The diagonal
+    // of row rr < 16 belongs to thread rr (q = 0), whose myup it is.
+    const int to = wg_tid<NT>();
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
-        const int rr = tid + NT * q;
-        if (rr < nrows || (WgShared<NT, QM>::ROWS && rr < ((nrows + 15) & ~15))) {
+        const int rr = to + NT * q;
+        if (rr < nrows) {
 #pragma unroll
-            for (int j = 0; j < WG_P; ++j) sh.v[sh.vi(rr, j)] = a[q][j];   // zeros past nrows
+            for (int j = 0; j < WG_P; ++j) {
+                if (j < pw) Ap[(size_t)j * lda + rr] = a[q][j];
+                const double v = (rr < j) ? 0.0 : ((rr == j) ? myup : a[q][j]);
+                sh.v[sh.vi(rr, j)] = (j < pw) ? v : 0.0;
+            }
+        } else if (WgShared<NT, QM>::ROWS && rr < ((nrows + 15) & ~15)) {
+            // the update by rows reads whole 16-row blocks
+#pragma unroll
+            for (int j = 0; j < WG_P; ++j) sh.v[sh.vi(rr, j)] = 0.0;
         }
     }
-    __syncthreads();
-#pragma unroll 1
-    for (int j = 0; j < pw; ++j) {
-        double *col = Ap + (size_t)j * lda;
-        for (int rr = tid; rr < nrows; rr += NT) col[rr] = sh.v[sh.vi(rr, j)];
-    }
-    __syncthreads();
-    if (tid < WG_P && tid < nrows) {
-#pragma unroll
-        for (int j = 0; j < WG_P; ++j) {
-            if (j >= tid) sh.v[sh.vi(tid, j)] = (j == tid) ? myup : 0.0;
-        }
-    }
-#pragma unroll 1
-    for (int j = pw; j < WG_P; ++j)
-        for (int rr = tid; rr < nrows; rr += NT) sh.v[sh.vi(rr, j)] = 0.0;
     __syncthreads();
     wg_panel_t<NT, QM>(nrows, pw, sh);
 }
@@ -1216,11 +1168,13 @@ __global__ void __launch_bounds__(WG_ROWS_NT) wg_batched_rows_kernel(const WgDes
     }
 }
 
-// One problem, descriptor by value (info slot d.index of `info`).
+// One problem, descriptor by value (info slot d.index of `info`); iters, if
+// given, gets 0.
 template <int NT, int QM, int PIPE>
-__global__ void __launch_bounds__(NT) wg_single_kernel(WgDesc d, int *info)
+__global__ void __launch_bounds__(NT) wg_single_kernel(WgDesc d, int *info, int *iters)
 {
     __shared__ WgShared<NT, QM> sh;
+    if (iters && threadIdx.x == 0) *iters = 0;
     wg_instance<NT, QM, PIPE>(d, info, sh);
 }
 

@@ -9,7 +9,7 @@ namespace hqr {
 namespace {
 
 typedef void (*wg_batched_fn)(const WgDesc *, int, int *, int *);
-typedef void (*wg_single_fn)(WgDesc, int *);
+typedef void (*wg_single_fn)(WgDesc, int *, int *);
 
 struct WgKernels {
     wg_batched_fn batched;
@@ -60,9 +60,9 @@ const WgVariant *wg_variants(int *count)
     return v;
 }
 
-hipError_t k_wg_single(const WgVariant *v, hipStream_t s, const WgDesc &d, int *info)
+hipError_t k_wg_single(const WgVariant *v, hipStream_t s, const WgDesc &d, int *info, int *iters)
 {
-    HQR_LAUNCH(K_SMALL, kernels[v->index].single, dim3(1), dim3(v->nt), 0, s, d, info);
+    HQR_LAUNCH(K_SMALL, kernels[v->index].single, dim3(1), dim3(v->nt), 0, s, d, info, iters);
     return hipGetLastError();
 }
 
