@@ -169,7 +169,7 @@ struct TrsvArgs {
     const int *active; // optional: nothing to do when *active == 0
 };
 
-constexpr int TRSV_MAXRHS = 8;
+constexpr int TRSV_MAXRHS = 8, TRSV_ROWS = 128;
 // A signalling NaN with a nonzero payload, the same 32-bit word twice (so the
 // integer fill writes it).  Arithmetic returns only quiet NaNs, and a value
 // that matched the pattern would be published as the default quiet NaN, so a

@@ -19,6 +19,8 @@
 // data, in the same order, by every workgroup.
 #pragma once
 
+#include <utility>
+
 #include "hqr_args.hpp"
 
 #define HQR_HD __host__ __device__
@@ -616,159 +618,262 @@ __global__ void __launch_bounds__(256) diag_check_kernel(const double *A, int64_
 
 
 
-// Workgroup b owns row block b (64 rows; for TRANS, R^T x = b by forward
-// substitution and the blocks above it).  Everything that does not depend on
-// other blocks is loaded before the first wait: the diagonal block (with the
-// reciprocals of its diagonal), the block's right-hand sides, and each
-// off-diagonal block of R one iteration ahead, in registers.  The remaining
-// critical path per block is: poll the predecessor's x values until none
-// holds TRSV_EMPTY (one read of memory shared by all XCDs, no separate flag
-// and no cache invalidation), one 64 x 64 block product, a 64-step
-// substitution with multiplies by the precomputed reciprocals, and the
-// stores that publish the result (no release fence: no other data rides on
-// them).  NR: right-hand sides handled per pass (1, or TRSV_MAXRHS for
-// 2..8); the four waves take the right-hand sides' substitutions in turn.
-template <bool TRANS, int NR>
-__global__ void __launch_bounds__(256) trsv_kernel(TrsvArgs p)
+// Workgroup b owns TRSV_ROWS = 128 rows (for TRANS, R^T x = b by forward
+// substitution and the blocks above it).  Positions 0 .. 127 are its rows in
+// the order in which they are solved.  Everything that does not depend on
+// other blocks is loaded before the first wait: the diagonal block, the
+// block's right-hand sides, and each 64-column off-diagonal block of R one
+// iteration ahead, in registers.  The critical path per block is then: poll
+// the predecessor's last 64 x values until none holds TRSV_EMPTY (one read of
+// memory shared by all XCDs, no separate flag and no cache invalidation), one
+// 128 x 64 block product, a 128-step substitution with multiplies by the
+// precomputed reciprocals, and the stores that publish the results, 64 at a
+// time (no release fence: no other data rides on them).
+//
+// Bound: the serial chain of n steps and the handoffs between workgroups
+// (about 1.5 us each).  One wave solves one right-hand side, lane l holding
+// positions l and 64 + l: a step is a multiply, two lane reads and an FMA on
+// the chain, and the second position's FMA beside it.  No step masks the
+// positions already solved: their entries are stored as zeros.  Zero times a
+// value that is not finite would change them, so a half that holds one is
+// solved again with the masks.  Against 64-row blocks with masked steps and
+// 1 or 8 right-hand sides per pass: 221 -> 141 us at n = 4096, one right-hand
+// side; 167 -> 82 at n = 2000, four; R^T x = b at n = 2048, two: 160 -> 67.
+// NR: right-hand sides of a pass (1, 2, 4 or 8).
+constexpr int TRSV_NT = 512;
+
+typedef double f64x4u __attribute__((ext_vector_type(4), aligned(8)));   // any element address
+
+struct TrsvLane {
+    double t0, t1;     // the running right-hand sides of positions l, 64 + l
+    double r0, r1;     // 1 / diagonal
+};
+
+// position Q (of the half HALF): solves it and updates the rest; e0, e1 are
+// the matrix entries of this position's column at l and 64 + l
+template <int HALF, int Q> HQR_DEV void trsv_step(TrsvLane &s, double e0, double e1)
 {
-    __shared__ double xs[64][NR];
-    __shared__ double accs[64][NR];
-    __shared__ double part[4][64][NR];
-    __shared__ double Rd[64][65];
-    __shared__ double rinv[64];
-    __shared__ int bad;
-    const int tid = threadIdx.x, lane = tid & 63, g = tid >> 6;
+    const double xi = readlane_f64(HALF ? s.t1 * s.r1 : s.t0 * s.r0, Q);
+    if (HALF == 0) s.t0 = fma(-e0, xi, s.t0);
+    s.t1 = fma(-e1, xi, s.t1);
+}
+
+template <int HALF, int G, int... I>
+HQR_DEV void trsv_steps(TrsvLane &s, const double (&e0)[16], const double (&e1)[16], std::integer_sequence<int, I...>)
+{
+    (trsv_step<HALF, 16 * G + I>(s, e0[I], e1[I]), ...);
+}
+
+// 16 steps with the next 16 columns' entries being read meanwhile; ends early
+// at the last group that holds one of the nr rows
+template <int HALF, int G>
+HQR_DEV void trsv_half(TrsvLane &s, const double *S, int nr, int lane, double (&e0)[16], double (&e1)[16])
+{
+    constexpr int LD = HALF ? 65 : 129;
+    double f0[16], f1[16];
+    if constexpr (G < 3) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double *col = S + (16 * (G + 1) + i) * LD;
+            if (HALF == 0) f0[i] = col[lane];
+            f1[i] = col[(HALF ? 0 : 64) + lane];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    trsv_steps<HALF, G>(s, e0, e1, std::make_integer_sequence<int, 16>{});
+    if constexpr (G < 3) {
+        if (nr > 64 * HALF + 16 * (G + 1)) trsv_half<HALF, G + 1>(s, S, nr, lane, f0, f1);
+    }
+}
+
+// the same with the solved positions left alone, for values that are not
+// finite: returns the solution of position lane of the half
+template <int HALF> HQR_DEV double trsv_masked(TrsvLane &s, const double *S, int nr, int lane)
+{
+    constexpr int LD = HALF ? 65 : 129;
+    double x = 0.0;
+    const int nq = min(nr - 64 * HALF, 64);
+    for (int q = 0; q < nq; ++q) {
+        const double xi = readlane_f64(HALF ? s.t1 * s.r1 : s.t0 * s.r0, q);
+        if (HALF == 0 && lane > q) s.t0 = fma(-S[q * LD + lane], xi, s.t0);
+        if (HALF == 0 || lane > q) s.t1 = fma(-S[q * LD + (HALF ? 0 : 64) + lane], xi, s.t1);
+        x = (lane == q) ? xi : x;
+    }
+    return x;
+}
+
+template <bool TRANS, int NR>
+__global__ void __launch_bounds__(TRSV_NT) trsv_kernel(TrsvArgs p)
+{
+    // S1[q][l]: entry of position q < 64 in the row of position l; S2[q][l]:
+    // of position 64 + q in that of 64 + l
+    __shared__ double S1[64][129], S2[64][65];
+    __shared__ double xs[2][NR][64];
+    __shared__ double part[4][NR][TRSV_ROWS];
+    __shared__ int bad[2];
+    const int tid = threadIdx.x, lane = tid & 63, pos = tid & (TRSV_ROWS - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), g = w >> 1;
     if (*((volatile int *)p.info) != 0) return;
     if (p.active && *((volatile int *)p.active) == 0) return;
-    const int nblk = (int)((p.n + 63) / 64);
+    const int nblk = (int)((p.n + TRSV_ROWS - 1) / TRSV_ROWS);
     const int ib = TRANS ? (int)blockIdx.x : nblk - 1 - (int)blockIdx.x;
-    const int64_t r0 = (int64_t)ib * 64;
-    const int nr = (int)min<int64_t>(64, p.n - r0);
+    const int64_t r0 = (int64_t)ib * TRSV_ROWS;
+    const int nr = (int)min<int64_t>(TRSV_ROWS, p.n - r0);
     const int nrhs = p.nrhs;
-    if (tid == 0) bad = 0;
-    // independent of the other blocks: diagonal block, own right-hand sides
-    for (int idx = tid; idx < nr * nr; idx += 256) {
-        const int cc = idx / nr, r = idx - cc * nr;
-        Rd[r][cc] = HQR_AT(p.A, r0 + r, r0 + cc, p.lda);
-    }
-    for (int idx = tid; idx < nr * NR; idx += 256) {
-        const int c = idx / nr, r = idx - c * nr;
-        accs[r][c] = (c < nrhs) ? HQR_AT(p.B, r0 + r, c, p.ldb) : 0.0;
-    }
-    double acc[NR];
-#pragma unroll
-    for (int c = 0; c < NR; ++c) acc[c] = 0.0;
-    const int npred = TRANS ? ib : nblk - 1 - ib;
-    // off-diagonal block of iteration jj: thread (row lane, group g) takes
-    // columns g, g + 4, .., of the predecessor block
+    // row of position q; positions past the block repeat its last one (their
+    // values are computed last and go nowhere)
+    auto row = [&](int q) { return r0 + (TRANS ? min(q, nr - 1) : nr - 1 - min(q, nr - 1)); };
+    if (tid < 2) bad[tid] = 0;
+    // off-diagonal 64-column block of iteration jj: thread (position fp, group
+    // fg) takes 16 of its columns.  TRANS reads rows of R^T, which lie along
+    // R's columns: the four groups of a position are lanes of one wave and
+    // take 4 consecutive elements of each 16, so that a load covers whole
+    // lines of 16 columns (one position per lane touches 64 lines per load:
+    // 141 us against 67 at n = 2048)
+    const int nhalf = (int)((p.n + 63) / 64);
+    const int npred = TRANS ? 2 * ib : max(nhalf - 2 * (ib + 1), 0);
+    const int fp = TRANS ? 16 * w + (lane & 15) : pos, fg = TRANS ? lane >> 4 : g;
+    const int64_t prow = row(fp);
+    auto col = [&](int q) { return TRANS ? 16 * (q >> 2) + 4 * fg + (q & 3) : 16 * fg + q; };
     auto fetch = [&](int jj, double (&rv)[16]) {
-        const int jb = TRANS ? jj : nblk - 1 - jj;
-        const int64_t c0 = (int64_t)jb * 64;
-        const int nc = (int)min<int64_t>(64, p.n - c0);
+        const int64_t c0 = (int64_t)(TRANS ? jj : nhalf - 1 - jj) * 64;
+        if constexpr (TRANS) {   // 64 columns: only the last block has fewer
+            const double *src = p.A + (size_t)prow * p.lda + c0 + 4 * fg;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int l = g + 4 * q;
-            rv[q] = (lane < nr && l < nc) ? (TRANS ? HQR_AT(p.A, c0 + l, r0 + lane, p.lda) : HQR_AT(p.A, r0 + lane, c0 + l, p.lda))
-                                          : 0.0;
+            for (int q = 0; q < 4; ++q) {
+                const f64x4u v = *(const f64x4u *)(src + 16 * q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rv[4 * q + e] = v[e];
+            }
+        } else {
+            const int nc = (int)min<int64_t>(64, p.n - c0);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) rv[q] = HQR_AT(p.A, prow, c0 + min(col(q), nc - 1), p.lda);
         }
     };
     double rv[16], rn[16];
     if (npred > 0) fetch(0, rv);
+    // independent of the other blocks: the diagonal block, reciprocals of its
+    // diagonal and own right-hand sides (wave c: right-hand side c)
+    {
+        double v1[16], v2[8];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int q = TRANS ? lane : g + 4 * k, l = TRANS ? w + 8 * k : pos;
+            v1[k] = TRANS ? HQR_AT(p.A, row(q), row(l), p.lda) : HQR_AT(p.A, row(l), row(q), p.lda);
+        }
+        if (nr > 64) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int q = TRANS ? lane : w + 8 * k, l = TRANS ? w + 8 * k : lane;
+                v2[k] = TRANS ? HQR_AT(p.A, row(64 + q), row(64 + l), p.lda) : HQR_AT(p.A, row(64 + l), row(64 + q), p.lda);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int q = TRANS ? lane : g + 4 * k, l = TRANS ? w + 8 * k : pos;
+            S1[q][l] = (l > q) ? v1[k] : 0.0;
+        }
+        if (nr > 64) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int q = TRANS ? lane : w + 8 * k, l = TRANS ? w + 8 * k : lane;
+                S2[q][l] = (l > q) ? v2[k] : 0.0;
+            }
+        }
+    }
+    TrsvLane sl;
+    const bool solver = w < nrhs && w < NR;
+    if (solver) {
+        const int64_t ra = row(lane), rb = row(64 + lane);
+        sl.t0 = HQR_AT(p.B, ra, w, p.ldb);
+        sl.t1 = HQR_AT(p.B, rb, w, p.ldb);
+        sl.r0 = 1.0 / HQR_AT(p.A, ra, ra, p.lda);
+        sl.r1 = 1.0 / HQR_AT(p.A, rb, rb, p.lda);
+        pin_f64(sl.r0);
+        pin_f64(sl.r1);
+    }
+    double acc[NR];
+#pragma unroll
+    for (int c = 0; c < NR; ++c) acc[c] = 0.0;
     __syncthreads();
-    if (tid < nr) rinv[tid] = 1.0 / Rd[tid][tid];
+    // two buffers of x and of the timeout flag, one barrier per iteration: a
+    // buffer is written again only past the next iteration's barrier
     for (int jj = 0; jj < npred; ++jj) {
-        const int jb = TRANS ? jj : nblk - 1 - jj;
         if (jj + 1 < npred) fetch(jj + 1, rn);
-        const int64_t c0 = (int64_t)jb * 64;
+        const int64_t c0 = (int64_t)(TRANS ? jj : nhalf - 1 - jj) * 64;
         const int nc = (int)min<int64_t>(64, p.n - c0);
-        for (int idx = tid; idx < 64 * NR; idx += 256) {
-            const int r = idx / NR, c = idx - r * NR;
+        if (w < NR) {
             unsigned long long u = 0;   // the bits of +0.0
-            if (r < nc && c < nrhs) {
-                unsigned long long *slot = (unsigned long long *)(p.xpub + (size_t)c * p.n + (size_t)(c0 + r));
+            if (lane < nc && w < nrhs) {
+                unsigned long long *slot = (unsigned long long *)(p.xpub + (size_t)w * p.n + (size_t)(c0 + lane));
                 long spins = 0;
                 while ((u = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == TRSV_EMPTY) {
                     if (++spins > p.spin_limit) {
-                        bad = 1;
+                        bad[jj & 1] = 1;
                         break;
                     }
                     __builtin_amdgcn_s_sleep(1);
                 }
             }
-            xs[r][c] = __longlong_as_double((long long)u);
+            xs[jj & 1][w][lane] = __longlong_as_double((long long)u);
         }
         __syncthreads();
-        if (bad) break;
+        if (bad[jj & 1]) {
+            if (tid == 0) atomicExch(p.info, HQR_INFO_TIMEOUT);
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const int l = g + 4 * q;
+            const double a = (col(q) < nc) ? rv[q] : 0.0;
 #pragma unroll
-            for (int c = 0; c < NR; ++c) acc[c] = fma(rv[q], xs[l][c], acc[c]);
+            for (int c = 0; c < NR; ++c) acc[c] = fma(a, xs[jj & 1][c][col(q)], acc[c]);
         }
 #pragma unroll
         for (int q = 0; q < 16; ++q) rv[q] = rn[q];
-        __syncthreads();
-    }
-    if (bad) {
-        if (tid == 0) atomicExch(p.info, HQR_INFO_TIMEOUT);
-        return;
     }
 #pragma unroll
-    for (int c = 0; c < NR; ++c) part[g][lane][c] = acc[c];
+    for (int c = 0; c < NR; ++c) part[fg][c][fp] = acc[c];
     __syncthreads();
-    if (g < nrhs && g < NR) {
-        // the substitution runs fully unrolled on registers: lane l holds its
-        // row (column when TRANS) of the diagonal block and 1/R_ll, so a step
-        // is two lane reads, a multiply and an FMA (no LDS access on the
-        // dependency chain).  Wave g solves right-hand sides g, g + 4.
-        double rowv[64];
-#pragma unroll
-        for (int i = 0; i < 64; ++i) rowv[i] = TRANS ? Rd[i][lane] : Rd[lane][i];
-        const double rl = (lane < nr) ? rinv[lane] : 0.0;
-        for (int c = g; c < nrhs && c < NR; c += 4) {
-            // fresh copies per right-hand side, so that the 64 steps' lane
-            // masks and lane reads are not hoisted out of this loop into
-            // hundreds of SGPRs (which spill to VGPR lanes and are read back
-            // at every step)
-            double rlc = rl;
-            pin_f64(rlc);
-            int lc = lane, nrc = nr;
-            asm volatile("" : "+v"(lc));
-            asm volatile("" : "+s"(nrc));
-            double t = 0.0;
-            if (lane < nr)
-                t = accs[lane][c] - (((part[0][lane][c] + part[1][lane][c]) + part[2][lane][c]) + part[3][lane][c]);
-            if (TRANS) {
-#pragma unroll
-                for (int i = 0; i < 64; ++i) {
-                    if (i < nrc) {
-                        const double xi = readlane_f64(t, i) * readlane_f64(rlc, i);
-                        if (lc > i && lc < nrc) t = fma(-rowv[i], xi, t);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int i = 63; i >= 0; --i) {
-                    if (i < nrc) {
-                        const double xi = readlane_f64(t, i) * readlane_f64(rlc, i);
-                        if (lc < i) t = fma(-rowv[i], xi, t);
-                    }
-                }
-            }
-            // lane l's value is final once step l has read it, so x_l is the
-            // same product t_l / R_ll (as t_l * rinv) that step l used; taking
-            // it here keeps a select off each step's dependency chain
-            t *= rl;
-            if (lane < nr) {
-                // publish first (the successors wait on it), then the result
-                unsigned long long u = (unsigned long long)__double_as_longlong(t);
-                if (u == TRSV_EMPTY) u = 0x7FF8000000000000ull;
-                __hip_atomic_store((unsigned long long *)(p.xpub + (size_t)c * p.n + (size_t)(r0 + lane)), u,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                p.B[(size_t)(r0 + lane) + (size_t)c * p.ldb] = t;
-            }
+    if (!solver) return;
+    sl.t0 -= ((part[0][w][lane] + part[1][w][lane]) + part[2][w][lane]) + part[3][w][lane];
+    sl.t1 -= ((part[0][w][64 + lane] + part[1][w][64 + lane]) + part[2][w][64 + lane]) + part[3][w][64 + lane];
+    // publish first (the successors wait on it), then the result
+    auto publish = [&](int q, double x) {
+        if (q < nr) {
+            const int64_t r = row(q);
+            unsigned long long u = (unsigned long long)__double_as_longlong(x);
+            if (u == TRSV_EMPTY) u = 0x7FF8000000000000ull;
+            __hip_atomic_store((unsigned long long *)(p.xpub + (size_t)w * p.n + (size_t)r), u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            p.B[(size_t)r + (size_t)w * p.ldb] = x;
         }
+    };
+    TrsvLane s0 = sl;
+    double e0[16], e1[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        e0[i] = S1[i][lane];
+        e1[i] = S1[i][64 + lane];
     }
+    trsv_half<0, 0>(sl, &S1[0][0], nr, lane, e0, e1);
+    double x = sl.t0 * sl.r0;
+    if (__ballot(lane < nr && !(fabs(x) < __builtin_inf()))) {
+        sl = s0;
+        x = trsv_masked<0>(sl, &S1[0][0], nr, lane);
+    }
+    publish(lane, x);
+    if (nr <= 64) return;
+    s0 = sl;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) e1[i] = S2[i][lane];
+    trsv_half<1, 0>(sl, &S2[0][0], nr, lane, e0, e1);
+    x = sl.t1 * sl.r1;
+    if (__ballot(64 + lane < nr && !(fabs(x) < __builtin_inf()))) {
+        sl = s0;
+        x = trsv_masked<1>(sl, &S2[0][0], nr, lane);
+    }
+    publish(64 + lane, x);
 }
 
 // resnorm[c] = ||B[n:m, c]||, one workgroup per column.

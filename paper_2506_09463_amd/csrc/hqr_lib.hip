@@ -206,7 +206,7 @@ static Plan make_plan(int64_t m, int64_t n, int64_t nrhs, int nb = NB, bool f32 
     p.nchunk = (int)((m + PC_ROWS - 1) / PC_ROWS);
     p.nxpad = (int)rup(NB + n + nrhs, 128);
     p.nsplit_max = 16;
-    p.nblk = (int)((n + 63) / 64);
+    p.nblk = (int)((n + TRSV_ROWS - 1) / TRSV_ROWS);
     p.ngroups = (int)((m + CQR_ROWS - 1) / CQR_ROWS);
     p.npanels = (int)((n + nb - 1) / nb);
     p.no_side = false;

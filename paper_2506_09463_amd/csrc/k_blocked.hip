@@ -50,15 +50,18 @@ hipError_t k_diag_check(hipStream_t s, const double *A, int64_t lda, int64_t n, 
     return hipGetLastError();
 }
 
+template <int NR> static void trsv_launch(bool trans, dim3 grid, hipStream_t s, const TrsvArgs &a)
+{
+    if (trans) HQR_LAUNCH(K_TRSV, (trsv_kernel<true, NR>), grid, dim3(TRSV_NT), 0, s, a);
+    else HQR_LAUNCH(K_TRSV, (trsv_kernel<false, NR>), grid, dim3(TRSV_NT), 0, s, a);
+}
+
 hipError_t k_trsv(bool trans, int nrhs, dim3 grid, hipStream_t s, const TrsvArgs &a)
 {
-    if (nrhs == 1) {
-        if (trans) HQR_LAUNCH(K_TRSV, (trsv_kernel<true, 1>), grid, dim3(256), 0, s, a);
-        else HQR_LAUNCH(K_TRSV, (trsv_kernel<false, 1>), grid, dim3(256), 0, s, a);
-    } else {
-        if (trans) HQR_LAUNCH(K_TRSV, (trsv_kernel<true, TRSV_MAXRHS>), grid, dim3(256), 0, s, a);
-        else HQR_LAUNCH(K_TRSV, (trsv_kernel<false, TRSV_MAXRHS>), grid, dim3(256), 0, s, a);
-    }
+    if (nrhs == 1) trsv_launch<1>(trans, grid, s, a);
+    else if (nrhs == 2) trsv_launch<2>(trans, grid, s, a);
+    else if (nrhs <= 4) trsv_launch<4>(trans, grid, s, a);
+    else trsv_launch<TRSV_MAXRHS>(trans, grid, s, a);
     return hipGetLastError();
 }
 
