@@ -163,8 +163,8 @@ struct TrsvArgs {
     int64_t ldb;
     int64_t n;
     int nrhs;
-    double *xpub;    // [nrhs][n], every slot TRSV_EMPTY on entry
-    int *info;       // read: nonzero -> nothing to do; written on timeout
+    double *xpub;    // [nrhs][n], every slot TRSV_EMPTY when the solve starts
+    int *info;       // nonzero -> nothing to solve; written by the check and on timeout
     long spin_limit;
     const int *active; // optional: nothing to do when *active == 0
 };
@@ -439,7 +439,7 @@ hipError_t k_vtx(bool f32, bool with_v, dim3 grid, hipStream_t s, const VtxArgs 
 hipError_t k_tfactor(int panels, hipStream_t s, const TArgs &a);
 hipError_t k_wsolve(bool narrow, dim3 grid, hipStream_t s, const WArgs &a);
 hipError_t k_update(bool narrow, bool f32, dim3 grid, hipStream_t s, const UpdArgs &a);
-hipError_t k_diag_check(hipStream_t s, const double *A, int64_t lda, int64_t n, int *info);
+hipError_t k_trsv_begin(hipStream_t s, const TrsvArgs &a, bool check);
 hipError_t k_trsv(bool trans, int nrhs, dim3 grid, hipStream_t s, const TrsvArgs &a);
 hipError_t k_resnorm(dim3 grid, hipStream_t s, const double *B, int64_t ldb, int64_t n, int64_t m, double *out);
 hipError_t k_fill_int(hipStream_t s, int *p, int v, int64_t count);

@@ -902,8 +902,8 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
 static int backsolve_blocked(const Plan &pl, const Work &w, const double *A, int64_t lda, double *B, int64_t ldb,
                              int nrhs, int *info, hipStream_t s, bool trans = false, const int *active = nullptr)
 {
-    HQR_CK(k_diag_check(s, A, lda, pl.n, info));
-    for (int c = 0; c < nrhs; c += TRSV_MAXRHS) {
+    // without right-hand sides the diagonal is still checked
+    for (int c = 0; c == 0 || c < nrhs; c += TRSV_MAXRHS) {
         TrsvArgs t;
         t.A = A;
         t.lda = lda;
@@ -911,12 +911,12 @@ static int backsolve_blocked(const Plan &pl, const Work &w, const double *A, int
         t.ldb = ldb;
         t.n = pl.n;
         t.nrhs = std::min(TRSV_MAXRHS, nrhs - c);
-        HQR_CK(k_fill_int(s, (int *)w.xpub, TRSV_EMPTY_WORD, 2 * pl.n * (int64_t)t.nrhs));
         t.xpub = w.xpub;
         t.info = info;
         t.spin_limit = 20000000L;
         t.active = active;
-        HQR_CK(k_trsv(trans, t.nrhs, dim3(pl.nblk), s, t));
+        HQR_CK(k_trsv_begin(s, t, c == 0));
+        if (t.nrhs > 0) HQR_CK(k_trsv(trans, t.nrhs, dim3(pl.nblk), s, t));
     }
     return 0;
 }

@@ -44,9 +44,10 @@ hipError_t k_update(bool narrow, bool f32, dim3 grid, hipStream_t s, const UpdAr
     return hipGetLastError();
 }
 
-hipError_t k_diag_check(hipStream_t s, const double *A, int64_t lda, int64_t n, int *info)
+hipError_t k_trsv_begin(hipStream_t s, const TrsvArgs &a, bool check)
 {
-    HQR_LAUNCH(K_DIAG, diag_check_kernel, dim3(1), dim3(256), 0, s, A, lda, n, info);
+    const int fill = (int)std::min<int64_t>((2 * a.n * (int64_t)a.nrhs + 255) / 256, 128);
+    HQR_LAUNCH(K_DIAG, trsv_begin_kernel, dim3(1 + fill), dim3(256), 0, s, a, check ? 1 : 0);
     return hipGetLastError();
 }
 
