@@ -758,7 +758,7 @@ __global__ void __launch_bounds__(256) cqr_gram1_kernel(Gram1Args p)
     __shared__ double M1[NB][LD65];
     __shared__ double M2[NB][LD65];
     __shared__ unsigned long long msk;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bw = p.bw, t = blockIdx.x;
     const int64_t rbase = p.upd ? (int64_t)p.cp : (int64_t)p.c0;
     const int64_t r0 = rbase + 64 * (int64_t)t;
@@ -789,22 +789,34 @@ __global__ void __launch_bounds__(256) cqr_gram1_kernel(Gram1Args p)
 #pragma unroll
         for (int q = 0; q < 4; ++q) st_blk(M0, 16 * w, 16 * q, acc[q], 1.0, lane);
         __syncthreads();
-        for (int idx = tid; idx < 64 * NB; idx += 256) {
-            const int c = idx / 64, r = idx % 64;
-            const int64_t gi = r0 + r;
-            if (gi < p.m && c < bw) HQR_AT(p.A, gi, p.c0 + c, p.lda) = M0[r][c];
-        }
+    }
+    // thread (row lane, columns w, w + 4, ..): all reads before the first use
+    double mv[16];
+    const int64_t gi = r0 + lane;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) mv[k] = M0[lane][w + 4 * k];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) pin_f64(mv[k]);
+    if (p.upd && gi < p.m) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (w + 4 * k < bw) HQR_AT(p.A, gi, p.c0 + w + 4 * k, p.lda) = mv[k];
     }
     if (flagged) return;                 // the exact loop factors this panel
     if (p.upd && t == 0) return;         // rows above the panel
     const int gidx = p.upd ? t - 1 : t;
+    // a wave's columns have one bit each: a ballot per column and one LDS
+    // atomic per wave.  The chain's latency binds here: with a branch and a
+    // wait per element and 256 atomics on one word the kernel took 16.5 us at
+    // 701 x 333, 13 so
     unsigned long long mymask = 0ull;
-    for (int idx = tid; idx < 64 * NB; idx += 256) {
-        const int c = idx / 64, r = idx % 64;
-        const int64_t gi = r0 + r;
-        if (c < bw && gi > (int64_t)p.c0 + c && gi < p.m && M0[r][c] != 0.0) mymask |= (1ull << c);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const int c = w + 4 * k;
+        const bool nz = c < bw && gi > (int64_t)p.c0 + c && gi < p.m && mv[k] != 0.0;
+        mymask |= (__ballot(nz) != 0ull) ? (1ull << c) : 0ull;
     }
-    if (mymask) atomicOr(&msk, mymask);
+    if (lane == 0 && mymask) atomicOr(&msk, mymask);
     f64x4 acc[4];
     gram64(acc, M0, lane, w);
     st64_global(p.gpart + (size_t)gidx * NB * NB, acc, lane, w);
@@ -818,7 +830,7 @@ __global__ void __launch_bounds__(256) cqr_gram2_kernel(Gram2Args p)
     __shared__ double X[NB][LD65];
     __shared__ double Y[NB][LD65];
     __shared__ double Ri[NB][LD65];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (*((volatile int *)p.flag)) return;
     const int t = blockIdx.x;
     const int64_t r0 = (int64_t)p.c0 + 64 * (int64_t)t;
@@ -832,11 +844,15 @@ __global__ void __launch_bounds__(256) cqr_gram2_kernel(Gram2Args p)
     __syncthreads();
     mm64(Y, X, Ri, lane, w);
     __syncthreads();
-    if (t == 0)
-        for (int idx = tid; idx < NB * NB; idx += 256) {
-            const int r = idx / NB, c = idx % NB;
-            p.q1top[idx] = (r < p.bw && c < p.bw) ? Y[r][c] : 0.0;
-        }
+    if (t == 0) {
+        double qv[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) qv[k] = Y[w + 4 * k][lane];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) pin_f64(qv[k]);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) p.q1top[tid + 256 * k] = (w + 4 * k < p.bw && lane < p.bw) ? qv[k] : 0.0;
+    }
     f64x4 acc[4];
     gram64(acc, Y, lane, w);
     st64_global(p.gpart + (size_t)t * NB * NB, acc, lane, w);
@@ -1239,7 +1255,7 @@ __global__ void __launch_bounds__(256) narrow_vtx_kernel(NarrowArgs p)
     __shared__ double M0[NB][LD65];
     __shared__ double M1[NB][LD65];
     __shared__ double M2[NB][LD65];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t = blockIdx.x;
     const int64_t r0 = (int64_t)p.c0 + 64 * (int64_t)t;
     const bool flagged = *((volatile int *)p.flag) != 0;
@@ -1275,10 +1291,14 @@ __global__ void __launch_bounds__(256) narrow_vtx_kernel(NarrowArgs p)
         for (int q = 0; q < 4; ++q) st_blk(M1, 16 * w, 16 * q, acc[q], 1.0, lane);
         __syncthreads();
         V = M1;
-        for (int idx = tid; idx < 64 * NB; idx += 256) {
-            const int c = idx / 64, r = idx % 64;
-            const int64_t gi = r0 + r;
-            if (gi < p.m) HQR_AT(p.A, gi, p.c0 + c, p.lda) = M1[r][c];
+        double vv[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) vv[k] = M1[lane][w + 4 * k];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) pin_f64(vv[k]);
+        if (r0 + lane < p.m) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) HQR_AT(p.A, r0 + lane, p.c0 + w + 4 * k, p.lda) = vv[k];
         }
     }
     // partial V_t^T C_t
