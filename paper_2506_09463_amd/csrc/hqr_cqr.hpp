@@ -55,7 +55,7 @@ HQR_DEV void mm64(double (*out)[LD65], const double (*A)[LD65], const double (*B
     f64x4 acc[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
+#pragma unroll
     for (int k0 = 0; k0 < NB; k0 += 4) {
         const int kr = k0 + (lane >> 4);
         const double a = A[16 * w + (lane & 15)][kr];
@@ -587,7 +587,7 @@ HQR_DEV void mat64_store(double (*M)[LD65], double (&v)[16], int tid)
 // acc[t] (t = 0..3) += sign * A[16w:16w+16][:] * B[:][16t:16t+16] over k = 0..63
 HQR_DEV void mm64_acc(f64x4 (&acc)[4], const double (*A)[LD65], const double (*B)[LD65], double sign, int lane, int w)
 {
-#pragma unroll 4
+#pragma unroll
     for (int k0 = 0; k0 < NB; k0 += 4) {
         const int kr = k0 + (lane >> 4);
         const double a = sign * A[16 * w + (lane & 15)][kr];
@@ -596,12 +596,16 @@ HQR_DEV void mm64_acc(f64x4 (&acc)[4], const double (*A)[LD65], const double (*B
     }
 }
 
-// acc[t] = Z^T Z (rows 16w.., column tile t) for a 64 x 64 LDS tile Z
+// acc[t] = Z^T Z (rows 16w.., column tile t) for a 64 x 64 LDS tile Z.  One
+// wave per SIMD: nothing hides an LDS read but the products before it, so the
+// 64-deep loops here and above are unrolled in full (by four, each group of 16
+// products waited for its reads: second Gram pass 9.8 us against 8.0 at
+// 701 x 333)
 HQR_DEV void gram64(f64x4 (&acc)[4], const double (*Z)[LD65], int lane, int w)
 {
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
+#pragma unroll
     for (int k0 = 0; k0 < NB; k0 += 4) {
         const int kr = k0 + (lane >> 4);
         const double a = Z[kr][16 * w + (lane & 15)];
@@ -1075,9 +1079,21 @@ __global__ void __launch_bounds__(256) cqr_chol_kernel(CholArgs p)
     HQR_TS();
 
     if (p.pass == 1) {
-        for (int idx = tid; idx < NB * NB; idx += 256) {
-            p.r1[idx] = M0[idx / NB][idx % NB];
-            p.r1inv[idx] = M1[idx / NB][idx % NB];
+        double rv[16], iv[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            rv[t] = M0[w + 4 * t][lane];
+            iv[t] = M1[w + 4 * t][lane];
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            pin(rv[t]);
+            pin(iv[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            p.r1[tid + 256 * t] = rv[t];
+            p.r1inv[tid + 256 * t] = iv[t];
         }
         return;
     }
@@ -1201,23 +1217,39 @@ __global__ void __launch_bounds__(256) cqr_chol_kernel(CholArgs p)
             p.T[r * NB + c] = (r <= c && c < bw) ? -v * (rupv[r] * rupv[c]) : 0.0;
         }, lane, w);
         for_uu(wacc, [&](int r, int c, double v) { p.winv[r * NB + c] = (c < bw) ? v * upv[c] : 0.0; }, lane, w);
-        for (int idx = tid; idx < NB * NB; idx += 256) {
-            const int i = idx / NB, j = idx % NB;
-            if ((i >> 4) > (j >> 4)) {
-                p.T[idx] = 0.0;
-                p.winv[idx] = 0.0;
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+            if (((w + 4 * t) >> 4) > (lane >> 4)) {
+                p.T[tid + 256 * t] = 0.0;
+                p.winv[tid + 256 * t] = 0.0;
             }
-        }
     }
     HQR_TS();
     // the panel's top block: R_house = S R on and above the diagonal, the
     // stored tails L[i][j] * up_j below it
-#pragma unroll 4
-    for (int idx = tid; idx < NB * NB; idx += 256) {
-        const int c = idx / NB, r = idx % NB;
-        const double *lp = ((r >> 4) == (c >> 4)) ? &DLL[r][c & 15] : &M2[r][c];
-        const double v = (r > c) ? *lp * upv[c] : sgn[r] * M0[r][c];
-        if (r < bw && c < bw) HQR_AT(p.A, (int64_t)p.c0 + r, p.c0 + c, p.lda) = v;
+    {
+        double tv[16], hv[16], uc[16], sr = sgn[lane];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            const int c = w + 4 * t;
+            const double *lp = ((lane >> 4) == (c >> 4)) ? &DLL[lane][c & 15] : &M2[lane][c];
+            tv[t] = *lp;
+            hv[t] = M0[lane][c];
+            uc[t] = upv[c];
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            pin(tv[t]);
+            pin(hv[t]);
+            pin(uc[t]);
+        }
+        if (lane < bw) {
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const int c = w + 4 * t;
+                if (c < bw) HQR_AT(p.A, (int64_t)p.c0 + lane, p.c0 + c, p.lda) = (lane > c) ? tv[t] * uc[t] : sr * hv[t];
+            }
+        }
     }
     HQR_TS();
 #undef HQR_TS
@@ -1229,7 +1261,7 @@ __global__ void __launch_bounds__(256) cqr_finish_kernel(FinArgs p)
     __shared__ double X[NB][LD65];
     __shared__ double Wi[NB][LD65];
     __shared__ double Y[NB][LD65];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (*((volatile int *)p.flag)) return;
     const int64_t r0 = (int64_t)p.c0 + p.bw + (int64_t)blockIdx.x * 64;
     {
@@ -1242,10 +1274,15 @@ __global__ void __launch_bounds__(256) cqr_finish_kernel(FinArgs p)
     __syncthreads();
     mm64(Y, X, Wi, lane, w);
     __syncthreads();
-    for (int idx = tid; idx < 64 * NB; idx += 256) {
-        const int c = idx / 64, r = idx % 64;
-        const int64_t gi = r0 + r;
-        if (gi < p.m && c < p.bw) HQR_AT(p.A, gi, p.c0 + c, p.lda) = Y[r][c];
+    double yv[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) yv[k] = Y[lane][w + 4 * k];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) pin_f64(yv[k]);
+    if (r0 + lane < p.m) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (w + 4 * k < p.bw) HQR_AT(p.A, r0 + lane, p.c0 + w + 4 * k, p.lda) = yv[k];
     }
 }
 
@@ -1306,7 +1343,7 @@ __global__ void __launch_bounds__(256) narrow_vtx_kernel(NarrowArgs p)
         f64x4 acc[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
+#pragma unroll
         for (int k0 = 0; k0 < NB; k0 += 4) {
             const int kr = k0 + (lane >> 4);
             const double a = V[kr][16 * w + (lane & 15)];
@@ -1329,6 +1366,9 @@ __global__ void __launch_bounds__(256) xw_reduce_kernel(XwArgs p)
     __shared__ double xc[64];
     const int tid = threadIdx.x, i = tid & 63, g4 = tid >> 6, j = blockIdx.x;
     const size_t e = (size_t)j * NB + i;
+    double tl[16];   // T's loads are in flight beside the partials'
+#pragma unroll
+    for (int u = 0; u < 16; ++u) tl[u] = p.T[(16 * g4 + u) * NB + i];
     double s = 0.0;
     for (int q0 = g4; q0 < p.parts; q0 += 64) {
         double v[16];
@@ -1342,15 +1382,12 @@ __global__ void __launch_bounds__(256) xw_reduce_kernel(XwArgs p)
 #pragma unroll
         for (int u = 0; u < 16; ++u) s += (q0 + 4 * u < p.parts) ? v[u] : 0.0;
     }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) pin_f64(tl[u]);
     part[g4][i] = s;
     __syncthreads();
     if (tid < 64) xc[i] = ((part[0][i] + part[1][i]) + part[2][i]) + part[3][i];
     __syncthreads();
-    double tl[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) tl[u] = p.T[(16 * g4 + u) * NB + i];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) pin_f64(tl[u]);
     double wv = 0.0;
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
