@@ -51,7 +51,7 @@ HBM_TRAFFIC = {
 }
 
 
-C2_KERNEL_SOURCES = ("hqr_args.hpp", "hqr_device.hpp", "hqr_blocked.hpp", "hqr_cqr.hpp", "k_blocked.hip",
+C2_KERNEL_SOURCES = ("hqr_args.hpp", "hqr_device.hpp", "hqr_blocked.hpp", "hqr_chol64.hpp", "hqr_cqr.hpp", "k_blocked.hip",
                      "k_cqr.hip")
 
 # HBM bytes of the batched workload's one launch (read, write), from the same
@@ -81,7 +81,8 @@ def wg_design_bytes(shapes, nrhs):
     """HBM bytes the one-workgroup kernel moves by design for instances of
     the given (m, n): per 16-column panel at c0 (m_p = m - c0 rows) the panel
     is read and written once and the later columns and the right-hand sides
-    are read twice and written once (W = V^T C, then C - V W'); then the
+    are read twice and written once (W = V^T C, then C - V W'; above 256 rows
+    C stays in registers between the two and is read once); then the
     triangle of R and B are read for the back-substitution."""
     tot = 0.0
     for m, n in shapes:
@@ -89,7 +90,7 @@ def wg_design_bytes(shapes, nrhs):
         for c0 in range(0, n, 16):
             pw = min(16, n - c0)
             mp = m - c0
-            tot += 16.0 * mp * pw + 24.0 * mp * ((n - c0 - pw) + nrhs)
+            tot += 16.0 * mp * pw + (16.0 if m > 256 else 24.0) * mp * ((n - c0 - pw) + nrhs)
         tot += 4.0 * n * n + 16.0 * m * nrhs
     return tot
 

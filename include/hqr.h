@@ -223,7 +223,7 @@ int hqr_cholesky(int64_t n, double *S, int64_t lds, void *work, int64_t lwork,
  * is the factor of the updated matrix; for the R of a QR factorization
  * (qr_factor's upper triangle, read in place with lda) it is the R of the
  * matrix with the row v^T appended.  v (n, device) is overwritten.  One
- * workgroup; n <= 4096 (else HQR_ENOTSUP).  Returns 0 or -i. */
+ * launch per 64 rows; n <= 4096 (else HQR_ENOTSUP).  Returns 0 or -i. */
 int hqr_chol_update(int64_t n, double *R, int64_t ldr, double *v,
                     hipStream_t stream);
 
@@ -302,14 +302,17 @@ int qr_lsq_batched_mixed(int count, const int64_t *m, const int64_t *n,
  *   op HQR_TUNE_SINGLE: path of one qr_factor / qr_apply_qt / qr_lsq_solve
  *     problem: choice -1 = the blocked multi-kernel path, choice i >= 0 = the
  *     one-workgroup kernel variant i (ignored where it cannot hold the
- *     problem).  Without a rule, problems with n <= 128 that a variant holds
+ *     problem; at most 128 rows and 32 columns with B run in one wave
+ *     whichever variant is named).  Without a rule, problems with n <= 128 that a variant holds
  *     use the smallest such variant.
  *   op HQR_TUNE_BATCHED: variant i of a batched launch, matched on the
  *     largest m and n among the batch's instances that the one-workgroup
  *     kernel takes (m <= 1024, n * nrhs within the smallest staging area);
  *     only variants with 256 threads qualify (they share one arithmetic, so
- *     results do not depend on the batch); without a rule, the smallest such
- *     variant that holds the largest m.
+ *     results do not depend on the batch); without a rule, instances above
+ *     256 rows take the 512-thread kernel and the rest the smallest such
+ *     variant that holds them.  A rule for a batch whose largest m is above
+ *     256 puts every instance on its variant.
  *   op HQR_TUNE_OCCUPANCY: workgroups per CU of the batched launch (choice
  *     1..8, capped by what the variant's LDS allows), matched like
  *     HQR_TUNE_BATCHED; without a rule, min(2, that cap).
