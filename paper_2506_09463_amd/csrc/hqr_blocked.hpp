@@ -176,28 +176,6 @@ HQR_DEV double v_elem_nb(const double *A, int64_t lda, const double *up, int c0,
     return (d < c) ? 0.0 : ((d == c) ? u : a);
 }
 
-// A 64 x 64 row-major matrix from global memory into LDS (transposed when
-// TRANS), by 256 threads: a thread's 16 loads are all issued before the first
-// is waited for (a plain copy loop waits on each load in turn).
-template <bool TRANS, int LD>
-HQR_DEV void ld64_lds(double (*M)[LD], const double *src, int tid)
-{
-    double v[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) v[t] = src[tid + 256 * t];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) pin_f64(v[t]);
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const int idx = tid + 256 * t;
-        if (TRANS)
-            M[idx % NB][idx / NB] = v[t];
-        else
-            M[idx / NB][idx % NB] = v[t];
-    }
-}
-
-
 // F32: operands rounded to FP32, FP32 MFMA with FP32 accumulation (the
 // partial sums are stored widened to FP64).  WITHV: the first bw X columns
 // are the panel's own V columns (the per-column panel mode forms V^T V there).
@@ -321,72 +299,76 @@ __global__ void __launch_bounds__(256, 2) vtx_kernel(VtxArgs p)
 
 
 
+// W' = T^T X (or T X) for COLS columns per workgroup: X summed from the
+// splits in order, then one 16-row tile of the product per wave on MFMA,
+// block columns beyond T's triangle skipped.
+//
+// Bound: latency (X is small).  The splits' loads of all of a thread's
+// elements and T's are in flight together; with one element after the other
+// and the product as scalar loops over LDS a launch took
+// 13.2 us in the wide Q application at 6001 x 700, 6.7 so.
+template <int COLS>
 __global__ void __launch_bounds__(256) wsolve_kernel(WArgs p)
 {
-    __shared__ double Ws[NB][WS_COLS + 1];
+    __shared__ double Ws[NB][COLS + 1];
     __shared__ double Ts[NB][NB + 1];
-    const int tid = threadIdx.x;
-    const int xb = p.xoff + blockIdx.x * WS_COLS;
-    const int xe = p.xoff + p.ncols;
-    ld64_lds<false>(Ts, p.T, tid);
-    // 1024 partial sums: thread t reduces elements (i = t / 4 + 64 q?) -- four per thread
+    constexpr int E = NB * COLS / 256, RS = 256 / COLS, U = 32 / E;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int xb = p.xoff + blockIdx.x * COLS, xe = p.xoff + p.ncols;
+    const int c = tid % COLS, i0 = tid / COLS;
+    double tv[16];
 #pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {
-        const int e = tid + 256 * e4;          // e in [0, 1024)
-        const int i = e / WS_COLS, c = e % WS_COLS;
-        const int x = xb + c;
-        double s = 0.0;
-        if (i < p.bw && x < xe) {
-            const double *src = p.wpart + (size_t)i * p.nxpad + x;
-            const size_t stride = (size_t)NB * p.nxpad;
-#pragma unroll 8
-            for (int q = 0; q < p.nsplit; ++q) s += src[q * stride];
-        }
-        Ws[i][c] = s;
+    for (int t = 0; t < 16; ++t) tv[t] = p.T[tid + 256 * t];
+    const double *src[E];
+    double s[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        src[k] = p.wpart + (size_t)min(i0 + RS * k, p.bw - 1) * p.nxpad + min(xb + c, xe - 1);
+        s[k] = 0.0;
+    }
+    const size_t stride = (size_t)NB * p.nxpad;
+    for (int q0 = 0; q0 < p.nsplit; q0 += U) {
+        double v[E][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < E; ++k) v[k][u] = src[k][(size_t)min(q0 + u, p.nsplit - 1) * stride];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < E; ++k) pin_f64(v[k][u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < E; ++k) s[k] += (q0 + u < p.nsplit) ? v[k][u] : 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < 16; ++t) pin_f64(tv[t]);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) Ts[w + 4 * t][lane] = tv[t];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        const int i = i0 + RS * k;
+        Ws[i][c] = (i < p.bw && xb + c < xe) ? s[k] : 0.0;
     }
     __syncthreads();
+    const int i16 = lane & 15, kk = lane >> 4, i = 16 * w + i16;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {
-        const int e = tid + 256 * e4;
-        const int i = e / WS_COLS, c = e % WS_COLS;
-        const int x = xb + c;
-        if (x >= xe) continue;
-        double s = 0.0;
-        if (p.tmode == 0) {
-            for (int l = 0; l <= i && l < p.bw; ++l) s += Ts[l][i] * Ws[l][c];
-        } else {
-            for (int l = i; l < p.bw; ++l) s += Ts[i][l] * Ws[l][c];
+    for (int kb = 0; kb < 4; ++kb) {
+        if (p.tmode == 0 ? kb > w : kb < w) continue;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 16 * kb + 4 * q + kk;
+            const double tr = (p.tmode == 0) ? Ts[k][i] : Ts[i][k];
+            const bool in = (p.tmode == 0) ? (k <= i && i < p.bw) : (k >= i && k < p.bw);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? tr : 0.0, Ws[k][i16 % COLS], acc, 0, 0, 0);
         }
-        p.wp[(size_t)i * p.nxpad + x] = (i < p.bw) ? s : 0.0;
     }
-}
-
-__global__ void __launch_bounds__(256) wsolve_narrow_kernel(WArgs p)
-{
-    __shared__ double Ws[NB][WSN_COLS + 1];
-    __shared__ double Ts[NB][NB + 1];
-    const int tid = threadIdx.x;
-    const int i = tid / WSN_COLS, c = tid % WSN_COLS;
-    const int x = p.xoff + blockIdx.x * WSN_COLS + c;
-    const int xe = p.xoff + p.ncols;
-    ld64_lds<false>(Ts, p.T, tid);
-    double s = 0.0;
-    if (i < p.bw && x < xe) {
-        const double *src = p.wpart + (size_t)i * p.nxpad + x;
-        const size_t stride = (size_t)NB * p.nxpad;
-#pragma unroll 16
-        for (int q = 0; q < p.nsplit; ++q) s += src[q * stride];
-    }
-    Ws[i][c] = s;
-    __syncthreads();
-    if (x < xe) {
-        double t = 0.0;
-        if (p.tmode == 0) {
-            for (int l = 0; l <= i && l < p.bw; ++l) t += Ts[l][i] * Ws[l][c];
-        } else {
-            for (int l = i; l < p.bw; ++l) t += Ts[i][l] * Ws[l][c];
-        }
-        p.wp[(size_t)i * p.nxpad + x] = (i < p.bw) ? t : 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 16 * w + 4 * r + kk, x = xb + i16;
+        if (i16 < COLS && x < xe) p.wp[(size_t)row * p.nxpad + x] = (row < p.bw) ? acc[r] : 0.0;
     }
 }
 

@@ -27,8 +27,8 @@ hipError_t k_vtx(bool f32, bool with_v, dim3 grid, hipStream_t s, const VtxArgs 
 
 hipError_t k_wsolve(bool narrow, dim3 grid, hipStream_t s, const WArgs &a)
 {
-    if (narrow) HQR_LAUNCH(K_WSOLVE, wsolve_narrow_kernel, grid, dim3(256), 0, s, a);
-    else HQR_LAUNCH(K_WSOLVE, wsolve_kernel, grid, dim3(256), 0, s, a);
+    if (narrow) HQR_LAUNCH(K_WSOLVE, wsolve_kernel<WSN_COLS>, grid, dim3(256), 0, s, a);
+    else HQR_LAUNCH(K_WSOLVE, wsolve_kernel<WS_COLS>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
