@@ -1028,6 +1028,7 @@ __global__ void __launch_bounds__(256) cqr_chol_kernel(CholArgs p)
             ql[t] = p.q1top[idx];
             rl[t] = p.r1[idx];
         }
+        __syncthreads();   // the flags are clear before any thread sets nonid_sh (the loads stay in flight)
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
             pin(gl[t]);
