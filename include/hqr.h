@@ -303,17 +303,16 @@ int qr_lsq_batched_mixed(int count, const int64_t *m, const int64_t *n,
  *     problem: choice -1 = the blocked multi-kernel path, choice i >= 0 = the
  *     one-workgroup kernel variant i (ignored where it cannot hold the
  *     problem; at most 128 rows and 32 columns with B run in one wave
- *     whichever variant is named).  Without a rule, problems with n <= 128 that a variant holds
- *     use the smallest such variant.
- *   op HQR_TUNE_BATCHED: variant i of a batched launch, matched on the
- *     largest m and n among the batch's instances that the one-workgroup
- *     kernel takes (m <= 1024, n * nrhs within the smallest staging area);
+ *     whichever variant is named).  Without a rule, problems with n <= 128
+ *     that a variant holds use the smallest such variant.
+ *   op HQR_TUNE_BATCHED: variant i for a batch's instances of at most 256
+ *     rows, matched on the largest m and n among those of them that the
+ *     one-workgroup kernel takes (n * nrhs within the smallest staging area);
  *     only variants with 256 threads qualify (they share one arithmetic, so
- *     results do not depend on the batch); without a rule, instances above
- *     256 rows take the 512-thread kernel and the rest the smallest such
- *     variant that holds them.  A rule for a batch whose largest m is above
- *     256 puts every instance on its variant.
- *   op HQR_TUNE_OCCUPANCY: workgroups per CU of the batched launch (choice
+ *     results do not depend on the batch or the rules); without a rule, the
+ *     smallest such variant that holds them.  Instances of 257 .. 1024 rows
+ *     take the 512-thread kernel whatever the rules say.
+ *   op HQR_TUNE_OCCUPANCY: workgroups per CU of that variant's launch (choice
  *     1..8, capped by what the variant's LDS allows), matched like
  *     HQR_TUNE_BATCHED; without a rule, min(2, that cap).
  * Host-side state, process-global, not thread-safe.  Returns 0 or -i. */

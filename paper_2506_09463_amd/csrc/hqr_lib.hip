@@ -84,9 +84,9 @@ static bool wg_fits(const WgVariant &v, int64_t m, int64_t n, int64_t nrhs)
 
 // Tuning rules (first match wins): op HQR_TUNE_SINGLE picks the path of one
 // problem (-1 = the blocked multi-kernel path, else a variant index), op
-// HQR_TUNE_BATCHED the variant of a batched launch from the batch's largest
-// m and n.  Without a matching rule: single problems with n <= 128 and
-// batches use the smallest variant that holds them.
+// HQR_TUNE_BATCHED the variant for a batch's instances of at most 256 rows,
+// from the largest m and n among them.  Without a matching rule: single
+// problems with n <= 128 and batches use the smallest variant that holds them.
 struct TuneRule {
     int op;
     int64_t mlo, mhi, nlo, nhi;
@@ -114,12 +114,14 @@ static const WgVariant *pick_wg_single(int64_t m, int64_t n, int64_t nrhs)
     return nullptr;
 }
 
-// Batched launches use only the variants with BATCH_NT threads: with the
-// thread count fixed, the rows each thread holds (QM) change no arithmetic
-// (row-to-thread map, reduction trees and tile order depend on NT alone), so
-// an instance's result does not depend on the rest of the batch.  Whether an
-// instance goes to the one-workgroup kernel also depends on its own shape
-// only: m <= BATCH_WG_ROWS and n * nrhs within the smallest staging area.
+// Batched instances of at most BATCH_NT rows, and the blocks of a TSQR tree,
+// use only the variants with BATCH_NT threads: with the thread count fixed,
+// the rows each thread holds (QM) change no arithmetic (row-to-thread map,
+// reduction trees and tile order depend on NT alone), so an instance's result
+// does not depend on the rest of the batch.  Whether an instance goes to the
+// one-workgroup kernels also depends on its own shape only: m <= BATCH_WG_ROWS
+// and n * nrhs within the smallest staging area; above BATCH_NT rows it takes
+// the 512-thread kernel.
 constexpr int BATCH_NT = 256;
 constexpr int64_t BATCH_WG_ROWS = 1024;
 
@@ -1272,33 +1274,27 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
         max_ntot = std::max<int>(max_ntot, (int)(n[i] + nrhs[i]));
     }
     // Four groups, each a launch of its own: instances above BATCH_NT rows
-    // (3: to factor, 2: stored) take 512 threads, whose update by rows keeps twice the bytes in
-    // flight and reads the trailing columns once per panel; smaller ones (1)
-    // a 256-thread variant, where a panel's steps, not its update, take the
-    // time; and what neither holds (0: more rows, or n * nrhs beyond the
-    // staging area) the streaming kernel.  The line depends on an instance's
-    // own rows only.  A tuning rule for the batch's largest instance puts the
-    // first three into one launch of the variant it names.  Each group runs
-    // longest first; ties keep caller order.
+    // (3: to factor, 2: stored) take 512 threads, whose update by rows keeps
+    // twice the bytes in flight and reads the trailing columns once per panel
+    // (2000 instances with n <= 512: 15.5 ms against 18.5 with 256 threads);
+    // smaller ones (1) a 256-thread variant, where a panel's steps, not its
+    // update, take the time; and what neither holds (0: more rows, or
+    // n * nrhs beyond the staging area) the streaming kernel.  The kernels
+    // round differently, so the line depends on an instance's own shape only,
+    // and tuning rules choose among the 256-thread variants (one arithmetic)
+    // from the third group's sizes.  Each group runs longest first; ties keep
+    // caller order.
     std::vector<char> fits((size_t)count);
     int64_t mmax = 0, nmax = 0;
     for (int i = 0; i < count; ++i) {
-        fits[i] = batch_wg_fits(m[i], n[i], nrhs[i]) ? 1 : 0;
-        if (fits[i]) {
+        if (!batch_wg_fits(m[i], n[i], nrhs[i])) {
+            fits[i] = 0;
+        } else if (m[i] > BATCH_NT) {
+            fits[i] = (factored && factored[i]) ? 2 : 3;
+        } else {
+            fits[i] = 1;
             mmax = std::max(mmax, m[i]);
             nmax = std::max(nmax, n[i]);
-        }
-    }
-    if (mmax > BATCH_NT && tune_lookup(HQR_TUNE_BATCHED, mmax, nmax, HQR_PREC_FP64) < 0) {
-        mmax = nmax = 0;
-        for (int i = 0; i < count; ++i) {
-            if (!fits[i]) continue;
-            if (m[i] > BATCH_NT) {
-                fits[i] = (factored && factored[i]) ? 2 : 3;
-            } else {
-                mmax = std::max(mmax, m[i]);
-                nmax = std::max(nmax, n[i]);
-            }
         }
     }
     const WgVariant *var = pick_wg_batched(mmax, nmax);
