@@ -747,6 +747,34 @@ static StreamCtx *stream_ctx(hipStream_t caller)
     return &c;
 }
 
+// Work put on a context's side stream between fork() and join().  The
+// destructor joins too: when a call returns early (a launch failed), the
+// caller's stream still waits for what runs on the side stream, which may
+// read the workspace that is freed next in the caller's stream order.
+struct SideFork {
+    StreamCtx *ctx = nullptr;
+    hipStream_t s = nullptr;
+    hipError_t fork(StreamCtx *c, hipStream_t caller)
+    {
+        hipError_t e = hipEventRecord(c->ev[3], caller);
+        if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->ev[3], 0);
+        if (e == hipSuccess) {
+            ctx = c;
+            s = caller;
+        }
+        return e;
+    }
+    hipError_t join()
+    {
+        if (!ctx) return hipSuccess;
+        hipError_t e = hipEventRecord(ctx->ev[2], ctx->side);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s, ctx->ev[2], 0);
+        ctx = nullptr;
+        return e;
+    }
+    ~SideFork() { (void)join(); }
+};
+
 static bool lookahead_enabled()
 {
     const char *e = getenv("HQR_LOOKAHEAD");
@@ -800,10 +828,10 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
         }
         return 0;
     }
-    hipEvent_t ev_a = ss->ev[0], ev_r = ss->ev[1], ev_join = ss->ev[2], ev_fork = ss->ev[3];
+    hipEvent_t ev_a = ss->ev[0], ev_r = ss->ev[1];
     // side stream starts after everything already on the caller's stream
-    HQR_CK(hipEventRecord(ev_fork, s));
-    HQR_CK(hipStreamWaitEvent(ss->side, ev_fork, 0));
+    SideFork fork;
+    HQR_CK(fork.fork(ss, s));
     bool pending_r = false;
     if (have_t) {
         // Fused chain on the caller's stream, per panel p:
@@ -858,8 +886,7 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
             }
             pending_r = true;
         }
-        HQR_CK(hipEventRecord(ev_join, ss->side));
-        HQR_CK(hipStreamWaitEvent(s, ev_join, 0));
+        HQR_CK(fork.join());
         return 0;
     }
     int rc = do_panel(0, (int)std::min<int64_t>(pl.nb, n), 0);
@@ -896,8 +923,7 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
         pending_r = true;
     }
     // join: the caller's stream waits for the last side-stream work
-    HQR_CK(hipEventRecord(ev_join, ss->side));
-    HQR_CK(hipStreamWaitEvent(s, ev_join, 0));
+    HQR_CK(fork.join());
     return 0;
 }
 
@@ -1344,11 +1370,12 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
     // longest factorizations leave (in one stream they would wait for the
     // last of them)
     hipStream_t s_rest = stream;
-    StreamCtx *ctx = nullptr;
-    if (nfac > 0 && nfac < nwg && (ctx = stream_ctx(stream)) != nullptr) {
-        HQR_CK(hipEventRecord(ctx->ev[3], stream));
-        HQR_CK(hipStreamWaitEvent(ctx->side, ctx->ev[3], 0));
-        s_rest = ctx->side;
+    SideFork fork;
+    if (nfac > 0 && nfac < nwg) {
+        if (StreamCtx *ctx = stream_ctx(stream)) {
+            HQR_CK(fork.fork(ctx, stream));
+            s_rest = ctx->side;
+        }
     }
     const WgDesc *wd = (const WgDesc *)dbase;
     if (nfac > 0) HQR_CK(k_wg_batched_rows(true, std::min(nfac, num_cus()), stream, wd, nfac, head + 2, info));
@@ -1361,10 +1388,7 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
         const int grid = std::min(nwg - nrow, occ * num_cus());
         HQR_CK(k_wg_batched(var, grid, s_rest, wd + nrow, nwg - nrow, head, info));
     }
-    if (ctx) {
-        HQR_CK(hipEventRecord(ctx->ev[2], ctx->side));
-        HQR_CK(hipStreamWaitEvent(stream, ctx->ev[2], 0));
-    }
+    HQR_CK(fork.join());
     if (nwg < count) {
         BatchArgs a;
         a.desc = (const BatchDesc *)(dbase + sizeof(WgDesc) * (size_t)nwg);

@@ -76,3 +76,11 @@ class HostLib:
         f = (ctypes.c_int * k)(*(factored or [0] * k))
         return self.lib.qr_lsq_batched_mixed(ctypes.c_int(k), i64(*m), i64(*n), i64(*r), p, i64(*m), p, p, i64(*m), p, f,
                                              info, None, ctypes.c_int64(0), None)
+
+    def factor(self, m, n):
+        """Status of qr_factor on an m x n problem, without a workspace."""
+        buf = np.zeros(16)
+        info = ctypes.c_int()
+        p = ctypes.c_void_p(buf.ctypes.data)
+        i64 = ctypes.c_int64
+        return self.lib.qr_factor(i64(m), i64(n), p, i64(m), p, None, i64(0), ctypes.byref(info), None)
