@@ -775,6 +775,7 @@ struct SideFork {
     ~SideFork() { (void)join(); }
 };
 
+// HQR_LOOKAHEAD=0: every call on the caller's stream alone.
 static bool lookahead_enabled()
 {
     const char *e = getenv("HQR_LOOKAHEAD");
@@ -1371,7 +1372,7 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
     // last of them)
     hipStream_t s_rest = stream;
     SideFork fork;
-    if (nfac > 0 && nfac < nwg) {
+    if (nfac > 0 && nfac < nwg && lookahead_enabled()) {
         if (StreamCtx *ctx = stream_ctx(stream)) {
             HQR_CK(fork.fork(ctx, stream));
             s_rest = ctx->side;

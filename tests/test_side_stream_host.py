@@ -50,3 +50,14 @@ def test_side_stream_is_joined_when_a_launch_fails(host, call):
         if not _joined(log):
             unjoined.append(next(l for l in log if l.startswith("failed")))
     assert unjoined == []
+
+
+@pytest.mark.parametrize("call", sorted(CALLS))
+def test_lookahead_switch_keeps_one_stream(host, call, monkeypatch):
+    monkeypatch.setenv("HQR_LOOKAHEAD", "0")
+    host.log()
+    assert CALLS[call](host) == 0
+    log = host.log()
+    assert any(l.startswith("launch") for l in log)
+    assert all("stream=0 " in l for l in log if l.startswith("launch"))
+    assert not any(l.startswith("wait") for l in log)
