@@ -5,17 +5,19 @@ Three decisions are tuned, each per shape bucket:
   * single problems (qr_lsq_solve, qr_factor, qr_apply_qt): the blocked
     multi-kernel path or one of the one-workgroup kernel variants (threads,
     rows per thread, trailing-update load depth), bucketed by (m, n); timed
-    on one seeded N(0,1) problem at the bucket's upper corner with one
-    right-hand side;
+    on seeded N(0,1) problems with one right-hand side, at the bucket's upper
+    corner, and where the two paths cross inside a bucket (129..256 rows and
+    columns) in finer buckets at their ends;
   * batched launches: the one-workgroup variant (256-thread variants only:
     rows per thread and load depth) together with the workgroups per CU of
     the persistent launch, bucketed by the batch's largest m; timed on a
     seeded batch of uneven instances (n ~ U{16..min(512, m_hi/2)},
     m = n + U{0..n}, 8 RHS).
-Every candidate that can hold the bucket's shape is run (exhaustive search,
+Every candidate that can hold the bucket's shapes is run (exhaustive search,
 as in the paper's parameter sweep of Section 4.1, here over kernel tile and
 schedule parameters instead of thread counts and chunk sizes); the fastest
-median wins.
+median wins (over several shapes: the smallest sum of times relative to each
+shape's fastest).
 
     python -m paper_2506_09463_amd.autotune --out tune_db.json
 
@@ -72,33 +74,58 @@ def _max_per_cu(name):
     return max(1, LDS_BYTES // lds)
 
 
-def tune_single(hqr, seed=11, reps=7, log=print):
+# 129..256 rows and columns, (m range, n range, square only): the blocked path
+# pays whole 64-column panels and, for a square problem, the exact loop on its
+# last panel (empty tail of the last column: 355 against 710 us at 193 x 192
+# and 192 x 192), the one-workgroup kernel grows with every column (239 us at
+# 129 x 129, 699 at 256 x 256), so the faster one changes inside the range.
+CROSSING = [((lo, hi), (lo, hi), True) for lo, hi in ((129, 160), (161, 192), (193, 240), (241, 256))]
+CROSSING += [((129, 256), (129, 144), False), ((145, 224), (145, 152), False), ((225, 256), (145, 152), False),
+             ((153, 224), (153, 160), False), ((225, 256), (153, 160), False), ((161, 192), (161, 168), False),
+             ((193, 256), (161, 168), False), ((169, 256), (169, 192), False), ((193, 256), (193, 256), False)]
+
+
+def single_buckets():
+    """(m range, n range, square only, shapes timed) in rule order: the first
+    bucket that holds a problem decides."""
+    out = []
+    for m, n, square in CROSSING:
+        if square:
+            shapes = [(k, k) for k in n]
+        else:
+            shapes = [(max(i, j + 1), j) for j in n for i in m if j < m[1]]
+        out.append((m, n, square, sorted(set(shapes))))
+    for m in M_BUCKETS:
+        for n in N_BUCKETS:
+            if n[0] <= m[1] and (m, n) != ((129, 256), (129, 256)):
+                out.append((m, n, False, [(m[1], min(n[1], m[1]))]))
+    return out
+
+
+def tune_single(hqr, seed=11, reps=7, log=print, buckets=None):
     import torch
     names = hqr.tune_variants()
     stream = torch.cuda.current_stream()
     rng = np.random.default_rng(seed)
     rules, meas = [], []
-    for (mlo, mhi) in M_BUCKETS:
-        for (nlo, nhi) in N_BUCKETS:
-            if nlo > mhi:
-                continue
-            m, n = mhi, min(nhi, mhi)
-            A_h = rng.standard_normal((m, n))
-            b_h = rng.standard_normal((m, 1))
-            A0, B0 = hqr.colmajor(A_h), hqr.colmajor(b_h)
+    for (mr, nr, square, shapes) in (single_buckets() if buckets is None else buckets):
+        score = {}
+        for (m, n) in shapes:
+            A0, B0 = hqr.colmajor(rng.standard_normal((m, n))), hqr.colmajor(rng.standard_normal((m, 1)))
             A, B = A0.clone(), B0.clone()
             up = torch.empty(n, dtype=torch.float64, device="cuda")
             res = torch.empty(1, dtype=torch.float64, device="cuda")
             info = torch.zeros(1, dtype=torch.int32, device="cuda")
+            work = torch.empty(hqr.workspace_size(m, n, 1), dtype=torch.uint8, device="cuda")   # kept, as a caller's is
 
             def restore():
                 A.copy_(A0)
                 B.copy_(B0)
 
             def run():
-                hqr.qr_lsq_solve(A, B, up=up, resnorm=res, info=info, stream=stream)
+                hqr.qr_lsq_solve(A, B, up=up, resnorm=res, info=info, work=work, stream=stream)
 
-            cands = ["blocked"] + [nm for nm in names if _variant_rows(nm)[1] >= m and _variant_rows(nm)[2] >= n]
+            cands = ["blocked"] + [nm for nm in names if _variant_rows(nm)[1] >= mr[1] and _variant_rows(nm)[2] >= nr[1]]
             times = {}
             for c in cands:
                 hqr.tune_clear()
@@ -109,11 +136,16 @@ def tune_single(hqr, seed=11, reps=7, log=print):
                 times[c] = _median_ms(run, reps, stream, restore)
             hqr.tune_clear()
             base = _median_ms(run, reps, stream, restore)  # built-in default
-            best = min(times, key=times.get)
-            meas.append({"op": "single", "m": [mlo, mhi], "n": [nlo, nhi], "shape": [m, n], "ms": times,
-                         "default_ms": base})
-            rules.append({"op": "single", "m": [mlo, mhi], "n": [nlo, nhi], "choice": best})
-            log("[tune] single m<=%d n<=%d: %s -> %s" % (mhi, nhi, {k: round(v, 4) for k, v in times.items()}, best))
+            for c in cands:
+                score[c] = score.get(c, 0.0) + times[c] / min(times.values())
+            meas.append({"op": "single", "m": list(mr), "n": list(nr), "shape": [m, n], "ms": times, "default_ms": base})
+        best = min(score, key=score.get)
+        rule = {"op": "single", "m": list(mr), "n": list(nr), "choice": best}
+        if square:
+            rule["square"] = True
+        rules.append(rule)
+        log("[tune] single m %s n %s%s at %s: %s -> %s" % (mr, nr, " square" if square else "", shapes,
+                                                          {k: round(v / len(shapes), 3) for k, v in score.items()}, best))
     return rules, meas
 
 

@@ -114,6 +114,16 @@ static const WgVariant *pick_wg_single(int64_t m, int64_t n, int64_t nrhs)
     return nullptr;
 }
 
+// A stored factor of more than 128 columns is applied by the blocked path
+// whatever the rules say: with every panel's T formed at once it takes 60 us
+// at 130 x 129 and 65 at 256 x 192 with up to 4 columns, the one-workgroup
+// kernel 129 and 225 (24 columns: 106 and 124 against 134 and 125); the
+// factorization's crossing, which the rules describe, lies elsewhere.
+static const WgVariant *pick_wg_apply(int64_t m, int64_t n, int64_t nrhs)
+{
+    return (n > 128) ? nullptr : pick_wg_single(m, n, nrhs);
+}
+
 // Batched instances of at most BATCH_NT rows, and the blocks of a TSQR tree,
 // use only the variants with BATCH_NT threads: with the thread count fixed,
 // the rows each thread holds (QM) change no arithmetic (row-to-thread map,
@@ -1051,7 +1061,7 @@ static int apply_stored(const Plan &pl, const Work &w, const double *A, int64_t 
 {
     const int64_t m = pl.m, n = pl.n;
     if (n == 0 || nrhs == 0) return 0;
-    if (const WgVariant *v = pick_wg_single(m, n, nrhs)) {
+    if (const WgVariant *v = pick_wg_apply(m, n, nrhs)) {
         const int64_t fl = (transpose ? 0 : WG_APPLY_Q) | (skip ? WG_QSKIP : 0);
         const WgDesc d{m, n, nrhs, lda, ldb, const_cast<double *>(A), B, const_cast<double *>(up), nullptr, 0, fl};
         return launch_wg_single(v, d, nullptr, s);
@@ -1488,7 +1498,7 @@ int qr_apply_qt(int64_t m, int64_t n, int64_t nrhs, const double *A, int64_t lda
     Plan pl = make_plan(m, n, nrhs);
     WorkGuard g;
     Work w;
-    if (!pick_wg_single(m, n, nrhs)) {
+    if (!pick_wg_apply(m, n, nrhs)) {
         const int rc = get_work(pl, work, lwork, stream, g, &w);
         if (rc) return rc;
     }
@@ -1511,7 +1521,7 @@ int qr_apply_q(int64_t m, int64_t n, int64_t nrhs, const double *A, int64_t lda,
     Plan pl = make_plan(m, n, nrhs);
     WorkGuard g;
     Work w;
-    if (!pick_wg_single(m, n, nrhs)) {
+    if (!pick_wg_apply(m, n, nrhs)) {
         const int rc = get_work(pl, work, lwork, stream, g, &w);
         if (rc) return rc;
     }
@@ -1536,7 +1546,7 @@ int qr_form_q(int64_t m, int64_t n, int64_t k, const double *A, int64_t lda, con
     Plan pl = make_plan(m, n, k);
     WorkGuard g;
     Work w;
-    if (!pick_wg_single(m, n, k)) {
+    if (!pick_wg_apply(m, n, k)) {
         const int rc = get_work(pl, work, lwork, stream, g, &w);
         if (rc) return rc;
     }

@@ -147,7 +147,8 @@ def tune_set(op, m_lo, m_hi, n_lo, n_hi, choice, precision=HQR_PREC_FP64):
 
 def load_tune_db(path=TUNE_DB_PATH):
     """Replace the rules with those of an autotuner database (JSON written by
-    paper_2506_09463_amd.autotune).  Variants are stored by name."""
+    paper_2506_09463_amd.autotune).  Variants are stored by name; a rule for
+    square problems becomes one rule per n."""
     import json
     with open(path) as f:
         db = json.load(f)
@@ -159,8 +160,12 @@ def load_tune_db(path=TUNE_DB_PATH):
         op = {"single": HQR_TUNE_SINGLE, "batched": HQR_TUNE_BATCHED, "occupancy": HQR_TUNE_OCCUPANCY}[r["op"]]
         if op == HQR_TUNE_OCCUPANCY:
             idx = int(choice)
-        tune_set(op, r["m"][0], r["m"][1], r["n"][0], r["n"][1], idx,
-                 HQR_PREC_MIXED if r.get("precision") == "mixed" else HQR_PREC_FP64)
+        prec = HQR_PREC_MIXED if r.get("precision") == "mixed" else HQR_PREC_FP64
+        if r.get("square"):
+            for k in range(max(r["m"][0], r["n"][0]), min(r["m"][1], r["n"][1]) + 1):
+                tune_set(op, k, k, k, k, idx, prec)
+        else:
+            tune_set(op, r["m"][0], r["m"][1], r["n"][0], r["n"][1], idx, prec)
 
 
 def status_string(status: int) -> str:

@@ -84,3 +84,10 @@ class HostLib:
         p = ctypes.c_void_p(buf.ctypes.data)
         i64 = ctypes.c_int64
         return self.lib.qr_factor(i64(m), i64(n), p, i64(m), p, None, i64(0), ctypes.byref(info), None)
+
+    def apply(self, m, n, nrhs):
+        """Status of qr_apply_qt with an m x n factor, without a workspace."""
+        buf = np.zeros(16)
+        p = ctypes.c_void_p(buf.ctypes.data)
+        i64 = ctypes.c_int64
+        return self.lib.qr_apply_qt(i64(m), i64(n), i64(nrhs), p, i64(m), p, p, i64(m), None, i64(0), None)
