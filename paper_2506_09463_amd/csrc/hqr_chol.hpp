@@ -43,13 +43,15 @@ struct CholArgsS {
     int *info;        // 0, or j+1 at the first non-positive pivot
 };
 
-// Whether an earlier block failed; the same answer for the whole workgroup
-// (the workgroup of the next diagonal block may write info meanwhile).
-HQR_DEV bool chol_failed(const int *info, int *sh)
+// Whether a pivot before row `before` failed; the same answer for every thread
+// of every workgroup: a launch passes the rows that were factored before it,
+// so a failure that its own workgroup 0 reports meanwhile does not count, and
+// each tile's update is either done in full or not at all.
+HQR_DEV bool chol_failed(const int *info, int64_t before, int *sh)
 {
     if (threadIdx.x == 0) *sh = *((volatile const int *)info);
     __syncthreads();
-    return *sh != 0;
+    return *sh != 0 && *sh <= before;
 }
 
 // A 64 x 64 tile of S at (r0, c0), rows < nr and columns < nc, zeros outside:
@@ -90,7 +92,7 @@ __global__ void __launch_bounds__(256) chol_panel_kernel(CholArgsS a)
     chol_tile_issue(sv, a.S, a.lds, a.k0, c0, a.bw, nc, tid);
 #pragma unroll
     for (int q = 0; q < 16; ++q) rv[q] = a.rinv[tid + 256 * q];
-    if (chol_failed(a.info, &failed)) return;
+    if (chol_failed(a.info, a.k0 + a.bw, &failed)) return;
     chol_tile_store(Sk, sv, a.bw, nc, tid);
 #pragma unroll
     for (int q = 0; q < 16; ++q) pin(rv[q]);
@@ -152,7 +154,7 @@ __global__ void __launch_bounds__(256) chol_syrk_kernel(CholArgsS a)
         const bool mirror = diag && r > c;
         sv[q] = HQR_AT(a.S, ri + (mirror ? c : r), cj + (mirror ? r : c), a.lds);
     }
-    if (chol_failed(a.info, &sh)) return;
+    if (chol_failed(a.info, t0, &sh)) return;
     if (a.bw > 0) {
         chol_tile_store(Ri, iv, a.bw, ni, tid);
         chol_tile_store(Rj, jv, a.bw, nj, tid);
@@ -181,6 +183,12 @@ __global__ void __launch_bounds__(256) chol_syrk_kernel(CholArgsS a)
     }
     chol64_dpp(Ri, Rj, ni, lane, w, 0.0, gdiag, rdiag, &sh);
     if (sh) {
+        // the block stays as its update left it
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int idx = tid + 256 * q, r = idx & 63, c = idx >> 6;
+            if (a.bw > 0 && r < ni && c < nj && r <= c) HQR_AT(a.S, ri + r, cj + c, a.lds) = sv[q];
+        }
         if (tid == 0) *((volatile int *)a.info) = (int)(ri + sh);
         return;
     }
