@@ -113,6 +113,46 @@ __global__ void __launch_bounds__(256) chol_panel_kernel(CholArgsS a)
     }
 }
 
+// What chol64_dpp does (ratio 0), with square roots and divisions that hold for
+// infinite pivots: x / inf = 0, where chol64_dpp's reciprocal roots give
+// inf * 0.  One column per step and four barriers: for blocks that have one.
+HQR_DEV void chol64_inf(double (*G)[LD65], double (*X)[LD65], int n, int tid, int *bad)
+{
+    __syncthreads();
+    if (tid == 0) *bad = 0;
+    for (int e = tid; e < NB * NB; e += 256) {
+        const int r = e >> 6, c = e & 63;
+        X[r][c] = 0.0;
+        if (r == c && r >= n) G[r][c] = 1.0;
+    }
+    __syncthreads();
+    for (int p = 0; p < n; ++p) {
+        const double piv = G[p][p];
+        if (!(piv > 0.0)) {   // the same for every thread
+            if (tid == 0) *bad = p + 1;
+            break;
+        }
+        const double rpp = sqrt(piv);
+        __syncthreads();
+        if (tid >= p && tid < NB) G[p][tid] = (tid == p) ? rpp : G[p][tid] / rpp;
+        __syncthreads();
+        for (int e = tid; e < NB * NB; e += 256) {
+            const int i = e >> 6, j = e & 63;
+            if (i > p && j >= i) G[i][j] -= G[p][i] * G[p][j];
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+    if (*bad == 0 && tid < NB) {
+        for (int i = tid; i >= 0; --i) {
+            double t = (i == tid) ? 1.0 : 0.0;
+            for (int l = i + 1; l <= tid; ++l) t -= G[i][l] * X[l][tid];
+            X[i][tid] = t / G[i][i];
+        }
+    }
+    __syncthreads();
+}
+
 // grid: the T (T + 1) / 2 upper tiles of the trailing matrix, T = ceil((n -
 // k0 - bw) / 64), column by column (tile 0 is the next diagonal block; one
 // tile when bw == 0): S_ij -= R_ki^T R_kj, on diagonal tiles the upper
@@ -176,12 +216,21 @@ __global__ void __launch_bounds__(256) chol_syrk_kernel(CholArgsS a)
     }
     if (blockIdx.x > 0) return;
     // the next diagonal block; the two triangles of its update agree bitwise
+    auto block = [&] {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int idx = tid + 256 * q, r = idx & 63, c = idx >> 6;
-        Ri[r][c] = (r < ni && c < nj) ? sv[q] : 0.0;
-    }
+        for (int q = 0; q < 16; ++q) {
+            const int idx = tid + 256 * q, r = idx & 63, c = idx >> 6;
+            Ri[r][c] = (r < ni && c < nj) ? sv[q] : 0.0;
+        }
+    };
+    block();
     chol64_dpp(Ri, Rj, ni, lane, w, 0.0, gdiag, rdiag, &sh);
+    // an infinite pivot leaves a NaN in rdiag (every wave sees all 64)
+    if (__ballot(lane < ni && !(rdiag[lane] < __builtin_inf()))) {
+        __syncthreads();
+        block();
+        chol64_inf(Ri, Rj, ni, tid, &sh);
+    }
     if (sh) {
         // the block stays as its update left it
 #pragma unroll
