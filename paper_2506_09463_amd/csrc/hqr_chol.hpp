@@ -274,7 +274,8 @@ HQR_DEV void rot_unpack(double rho, double &c, double &s)
 // The rotation of (a, b): r = sgn(a) hypot(a, b) with sgn(0) = +1, c = a / r,
 // s = b / r; (1, 0) and r = 0 when both are zero.  The fast form needs
 // d = a^2 + b^2 in [2^-900, 2^900] (one reciprocal square root, no division);
-// the other takes anything.
+// the other takes anything.  With b = 0 the fast form's c and r are 1 and a to
+// rounding only: its caller puts the row back.
 HQR_DEV void rot_fast(double a, double b, double d, double &c, double &s, double &r)
 {
     const double ri = pivot_rsqrt(d), bs = (a >= 0.0) ? b : -b;
@@ -437,9 +438,15 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
 #pragma unroll
             for (int i = 0; i < 16; ++i) D[lane][i0 + i] = a[i];
         }
+        const int64_t col = c0 + min(lane, nc - 1);
+        // a row whose rotation is none keeps its bits (a select in the steps
+        // lengthened their chain: 0.8 us a launch)
+        for (unsigned long long same = __ballot(lane < nc && cs[lane][1] == 0.0); same; same &= same - 1) {
+            const int k = __ffsll((long long)same) - 1;
+            D[lane][k] = HQR_AT(R, min(c0 + k, col), col, ldr);
+        }
         if (__ballot(lane < nc && !(my_d >= 0x1p-900 && my_d <= 0x1p900))) {
             vj = v0;
-            const int64_t col = c0 + min(lane, nc - 1);
             for (int k = 0; k < nc; ++k) {
                 const double x = HQR_AT(R, min(c0 + k, col), col, ldr);
                 double c, s, r;
