@@ -257,7 +257,7 @@ __global__ void __launch_bounds__(256) chol_syrk_kernel(CholArgsS a)
 // s / 2 when |s| < c, else sign(s) 2 / c (infinite when c = 0).
 HQR_DEV double rot_pack(double c, double s)
 {
-    return (fabs(s) < c) ? 0.5 * s : copysign(2.0 / c, s);
+    return (fabs(s) < c) ? 0.5 * s : ((s == s) ? copysign(2.0 / c, s) : s);   // NaN stays one
 }
 
 HQR_DEV void rot_unpack(double rho, double &c, double &s)

@@ -1,5 +1,5 @@
-"""hqr_chol_update where its rotations are exact: rows whose v is zero keep
-their bits."""
+"""hqr_chol_update where its rotations are exact or not finite: rows whose v is
+zero keep their bits, and values that are not finite spread as in the oracle."""
 import numpy as np
 import pytest
 
@@ -30,3 +30,17 @@ def test_rows_before_v_starts_keep_their_bits(n, first):
     F = _run(R, v)
     assert np.array_equal(F[:first], R[:first])
     assert first == n or not np.array_equal(F[first], R[first])
+
+
+@pytest.mark.parametrize("n,k", [(40, 3), (200, 3), (200, 70)])
+@pytest.mark.parametrize("rkk,vk", [(0.0, np.inf), (0.0, np.nan), (np.inf, 1.0), (2.0, -np.inf), (np.nan, 0.0)])
+def test_not_finite(oracle_mod, n, k, rkk, vk):
+    rng = np.random.default_rng(1950 + n + k)
+    R = np.triu(rng.standard_normal((n, n)) + 0.5)
+    v = rng.standard_normal(n)
+    R[k, k], v[k] = rkk, vk
+    print("[case] chol_update not finite", n, k, rkk, vk, flush=True)
+    F = _run(R, v)
+    with np.errstate(all="ignore"):
+        Ro = oracle_mod.chol_update(R, v)
+    assert np.array_equal(np.isfinite(F), np.isfinite(Ro))
