@@ -302,8 +302,8 @@ int qr_lsq_batched_mixed(int count, const int64_t *m, const int64_t *n,
  *   op HQR_TUNE_SINGLE: path of one qr_factor / qr_apply_qt / qr_lsq_solve
  *     problem: choice -1 = the blocked multi-kernel path, choice i >= 0 = the
  *     one-workgroup kernel variant i (ignored where it cannot hold the
- *     problem; at most 128 rows and 32 columns with B run in one wave
- *     whichever variant is named; a stored factor of more than 128 columns is
+ *     problem; the smallest, at most 128 rows and 32 columns with B, run in
+ *     one wave whichever variant is named; a stored factor of more than 128 columns is
  *     applied by the blocked path).  Without a rule, problems with n <= 128
  *     that a variant holds use the smallest such variant.
  *   op HQR_TUNE_BATCHED: variant i for a batch's instances of at most 256

@@ -163,13 +163,29 @@ static const WgVariant *pick_wg_batched(int64_t mmax, int64_t nmax)
     return best;
 }
 
-// One problem in one workgroup.  The smallest to factor (a wave holds them in
-// registers) take the kernel of few instructions instead of the variant's
-// panel kernel, up to the 128 rows and 32 columns its registers hold: 13.5
-// against 25 us per call at 20 x 8, 34 against 48 at 100 x 20.
+// Whether a problem to factor takes the one-wave kernel.  A wave's registers
+// hold 128 rows and 32 columns with B; there the kernel of few instructions is
+// faster as long as its solve, one right-hand side and one row after the
+// other, is short beside the factorization.  Measured against the panel kernel
+// (which pays per 16 columns) on m = 16, 32, 64, 65 and 128, times of the
+// panel kernel over ours: at most 16 columns with B 1.3 to 2.7; more, with at
+// most 15 to factor, 15 x 6 1.00, 15 x 8 0.93, 12 x 6 1.09, 12 x 12 0.90,
+// 8 x 12 1.04, 8 x 16 0.93, 4 x 24 0.96; one panel exactly, 16 x 2 1.02, 16 x 4
+// 0.93; two panels, 20 x 8 1.05, 20 x 12 0.92, 24 x 6 1.03, 24 x 8 0.96, 28 x 4
+// 1.03, 31 x 0 1.03, 32 x 0 0.94 (columns by right-hand sides; 16 x 16 with 16
+// took 58 us against 38).
+static bool tiny_fits(int64_t m, int64_t n, int64_t nrhs)
+{
+    if (m > TINY_ROWS || n + nrhs > TINY_COLS) return false;
+    if (n + nrhs <= 16) return true;
+    if (n == 16) return nrhs <= 2;
+    return n * nrhs <= (n < 16 ? 90 : 160) && n < 32;
+}
+
+// One problem in one workgroup.
 static int launch_wg_single(const WgVariant *v, const WgDesc &d, int *info, hipStream_t s, int *iters = nullptr)
 {
-    if ((d.flags & WG_FACTOR) && d.m <= TINY_ROWS && d.n + d.nrhs <= TINY_COLS)
+    if ((d.flags & WG_FACTOR) && tiny_fits(d.m, d.n, d.nrhs))
         return k_wg_tiny(s, d, info, iters) == hipSuccess ? 0 : HQR_EDEVICE;
     return k_wg_single(v, s, d, info, iters) == hipSuccess ? 0 : HQR_EDEVICE;
 }

@@ -91,3 +91,12 @@ class HostLib:
         p = ctypes.c_void_p(buf.ctypes.data)
         i64 = ctypes.c_int64
         return self.lib.qr_apply_qt(i64(m), i64(n), i64(nrhs), p, i64(m), p, p, i64(m), None, i64(0), None)
+
+    def lsq(self, m, n, nrhs):
+        """Status of qr_lsq_solve on an m x n problem, without a workspace."""
+        buf = np.zeros(16)
+        info = ctypes.c_int()
+        p = ctypes.c_void_p(buf.ctypes.data)
+        i64 = ctypes.c_int64
+        return self.lib.qr_lsq_solve(i64(m), i64(n), i64(nrhs), p, i64(m), p, p, i64(m), p, None, None, i64(m), None,
+                                     i64(0), ctypes.byref(info), None, None)
