@@ -1000,18 +1000,40 @@ static int get_work(const Plan &pl, void *work, int64_t lwork, hipStream_t s, Wo
     return 0;
 }
 
-// T of the leading npan stored panels into w.wp2 (64 x 64 each), in two
-// launches: partial V^T V by row splits (into w.wpart2), then one workgroup
-// per panel.  Both buffers are as wide as the whole matrix, so every panel's
-// part fits.  T does not depend on B: formed panel by panel it stood between
-// each panel's V^T B and its update (12 us a panel at 2047 x 1500).
+// T of the leading npan stored panels into w.wp2 (64 x 64 each): partial
+// V^T V of every panel by row splits in one launch, then one workgroup per
+// panel, which adds its splits up (at most nsplit_max of them, in w.wpart2).
+// Few panels of many rows leave most of the chip idle that way: above two
+// 64-row tiles a split with fewer than 256 workgroups, the splits are as many
+// as w.gpart holds (one 64 x 64 block per tile of the matrix) and a launch per
+// panel reduces them first.  Q^T b of 100000 x 64 took 496 us with 16 splits,
+// 141 so; 8192 x 64 73 and 43; at 1100 x 64 (18 tiles) 47 us either way.
+// wpart2 and wp2 are as wide as the whole matrix, so every panel's part fits.
+// T does not depend on B: formed panel by panel it stood between each panel's
+// V^T B and its update (12 us a panel at 2047 x 1500).
 static int stored_t(const Plan &pl, const Work &w, const double *A, int64_t lda, const double *up, int npan,
                     hipStream_t s)
 {
-    const int64_t tiles = (pl.m + 63) / 64;
-    const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)pl.nsplit_max, tiles, 512 / npan}));
-    const StoredGramArgs g{A, lda, up, pl.m, pl.n, w.wpart2};
+    const int64_t tiles = (pl.m + 63) / 64, fill = std::max(1, 512 / npan);
+    int nsplit = (int)std::min<int64_t>({(int64_t)pl.nsplit_max, tiles, fill});
+    const int many = (int)std::min<int64_t>({tiles, fill, (int64_t)pl.ngroups / npan});
+    const bool reduce = tiles > 2 * (int64_t)nsplit && npan * nsplit < 256 && many > nsplit;
+    if (reduce) nsplit = many;
+    double *part = reduce ? w.gpart : w.wpart2;
+    const StoredGramArgs g{A, lda, up, pl.m, pl.n, part};
     HQR_CK(k_stored_gram(npan, nsplit, s, g));
+    const size_t stride = (size_t)nsplit * NB * NB;
+    for (int p = 0; reduce && p < npan; ++p) {
+        GredArgs r;
+        r.gpart = part + p * stride;
+        r.ngroups = nsplit;
+        r.G = w.wpart2 + (size_t)p * NB * NB;
+        r.mask = w.mask;
+        r.mask_all = w.mask_all;
+        r.with_mask = 0;
+        r.flag = nullptr;
+        HQR_CK(k_gram_reduce(s, r));
+    }
     TArgs t;
     t.A = A;
     t.lda = lda;
@@ -1019,9 +1041,9 @@ static int stored_t(const Plan &pl, const Work &w, const double *A, int64_t lda,
     t.c0 = 0;
     t.bw = (int)std::min<int64_t>(pl.n, (int64_t)npan * NB);
     t.wpart = w.wpart2;
-    t.nsplit = nsplit;
+    t.nsplit = reduce ? 1 : nsplit;
     t.nxpad = NB;
-    t.wstride = (size_t)nsplit * NB * NB;
+    t.wstride = reduce ? (size_t)NB * NB : stride;
     t.T = w.wp2;
     HQR_CK(k_tfactor(npan, s, t));
     return 0;
