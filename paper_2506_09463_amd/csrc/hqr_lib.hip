@@ -1106,6 +1106,14 @@ static int apply_stored(const Plan &pl, const Work &w, const double *A, int64_t 
     }
     int npan = (int)((n + NB - 1) / NB);
     if (skip) npan = (int)std::min<int64_t>(npan, (nrhs + NB - 1) / NB);   // later panels meet no column
+    if (npan == 1 && nrhs > SN_COLS) {
+        // nothing to form beside other panels: V^T V in the pass of V^T B
+        // (1100 x 64, 17 columns: 55 us, 68 with a launch of its own; 100000 x
+        // 64: 411 and 780)
+        const int bw = (int)std::min<int64_t>(NB, n);
+        return apply_panel_block(pl, TrailBufs{w.wpart, w.T, w.wp}, const_cast<double *>(A), lda, B, ldb, up, 0, bw, 0,
+                                 0, (int)nrhs, false, s, false, 0, nullptr, 0, !transpose);
+    }
     const double *T = w.wp2;
     int rc = stored_t(pl, w, A, lda, up, npan, s);
     if (rc) return rc;

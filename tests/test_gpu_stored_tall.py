@@ -1,6 +1,7 @@
 """Applying a stored factorization where few panels have many rows (T from as
-many row splits as there are tiles, reduced first), against the oracle's
-application of the same reflectors within 50 n u max|B| sqrt(m)."""
+many row splits as there are tiles, reduced first) and where a single panel meets
+more than 16 columns (T in the pass of V^T B), against the oracle's application
+of the same reflectors within 50 n u max|B| sqrt(m)."""
 import numpy as np
 import pytest
 
