@@ -303,9 +303,10 @@ int qr_lsq_batched_mixed(int count, const int64_t *m, const int64_t *n,
  *     problem: choice -1 = the blocked multi-kernel path, choice i >= 0 = the
  *     one-workgroup kernel variant i (ignored where it cannot hold the
  *     problem; the smallest, at most 128 rows and 32 columns with B, run in
- *     one wave whichever variant is named; a stored factor of more than 128 columns is
- *     applied by the blocked path).  Without a rule, problems with n <= 128
- *     that a variant holds use the smallest such variant.
+ *     one wave whichever variant is named; a stored factor of more than 128
+ *     columns is applied by the blocked path, but for a small problem's first
+ *     columns of Q).  Without a rule, problems with n <= 128 that a variant
+ *     holds use the smallest such variant.
  *   op HQR_TUNE_BATCHED: variant i for a batch's instances of at most 256
  *     rows, matched on the largest m and n among those of them that the
  *     one-workgroup kernel takes (n * nrhs within the smallest staging area);

@@ -118,10 +118,16 @@ static const WgVariant *pick_wg_single(int64_t m, int64_t n, int64_t nrhs)
 // whatever the rules say: with every panel's T formed at once it takes 60 us
 // at 130 x 129 and 65 at 256 x 192 with up to 4 columns, the one-workgroup
 // kernel 129 and 225 (24 columns: 106 and 124 against 134 and 125); the
-// factorization's crossing, which the rules describe, lies elsewhere.
-static const WgVariant *pick_wg_apply(int64_t m, int64_t n, int64_t nrhs)
+// factorization's crossing, which the rules describe, lies elsewhere.  The
+// leading columns of Q (skip) need the reflectors up to theirs only: one
+// 16-column panel of the one-workgroup kernel for up to 16 of them, and a
+// whole 64-column panel of the blocked path (130 x 129, 3 columns: 29.6 and
+// 37.5 us, 32 columns 47.5 and 51.9; 256 x 256: 35.8 and 37.9, 58.7 and 49.2).
+static const WgVariant *pick_wg_apply(int64_t m, int64_t n, int64_t nrhs, bool skip = false)
 {
-    return (n > 128) ? nullptr : pick_wg_single(m, n, nrhs);
+    if (n <= 128) return pick_wg_single(m, n, nrhs);
+    if (skip && m <= 256 && nrhs <= (m <= 200 ? 32 : 16)) return pick_wg_single(m, std::min<int64_t>(nrhs, 16), nrhs);
+    return nullptr;
 }
 
 // Batched instances of at most BATCH_NT rows, and the blocks of a TSQR tree,
@@ -1099,7 +1105,7 @@ static int apply_stored(const Plan &pl, const Work &w, const double *A, int64_t 
 {
     const int64_t m = pl.m, n = pl.n;
     if (n == 0 || nrhs == 0) return 0;
-    if (const WgVariant *v = pick_wg_apply(m, n, nrhs)) {
+    if (const WgVariant *v = pick_wg_apply(m, n, nrhs, skip)) {
         const int64_t fl = (transpose ? 0 : WG_APPLY_Q) | (skip ? WG_QSKIP : 0);
         const WgDesc d{m, n, nrhs, lda, ldb, const_cast<double *>(A), B, const_cast<double *>(up), nullptr, 0, fl};
         return launch_wg_single(v, d, nullptr, s);
@@ -1592,7 +1598,7 @@ int qr_form_q(int64_t m, int64_t n, int64_t k, const double *A, int64_t lda, con
     Plan pl = make_plan(m, n, k);
     WorkGuard g;
     Work w;
-    if (!pick_wg_apply(m, n, k)) {
+    if (!pick_wg_apply(m, n, k, true)) {
         const int rc = get_work(pl, work, lwork, stream, g, &w);
         if (rc) return rc;
     }

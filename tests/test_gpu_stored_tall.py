@@ -1,7 +1,8 @@
 """Applying a stored factorization where few panels have many rows (T from as
-many row splits as there are tiles, reduced first) and where a single panel meets
-more than 16 columns (T in the pass of V^T B), against the oracle's application
-of the same reflectors within 50 n u max|B| sqrt(m)."""
+many row splits as there are tiles, reduced first), where a single panel meets
+more than 16 columns (T in the pass of V^T B), and the leading columns of Q of a
+small problem, against the oracle's application of the same reflectors within
+50 n u max|B| sqrt(m)."""
 import numpy as np
 import pytest
 
@@ -34,3 +35,14 @@ def test_tall_factor(oracle_mod, m, n, nrhs):
         fn(dA, up, dB)
         torch.cuda.synchronize()
         assert np.abs(to_host(dB) - ref(F, u, B)).max() <= tol
+
+
+@pytest.mark.parametrize("m,n", [(130, 129), (200, 150), (256, 256), (256, 200)])
+@pytest.mark.parametrize("k", [1, 16, 17, 32, 33, 100])
+def test_leading_columns_of_q(oracle_mod, m, n, k):
+    import torch
+    hqr, dA, up, F, u = _factor(m, n, 2500 + m + n)
+    print("[case] form_q", (m, n, k), flush=True)
+    Q = hqr.qr_form_q(dA, up, k=k)
+    torch.cuda.synchronize()
+    assert np.abs(to_host(Q) - oracle_mod.apply_q(F, u, np.eye(m, k))).max() <= 50 * n * U * np.sqrt(m)
