@@ -315,6 +315,7 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
     __shared__ double P[CHU][CHU + 1];   // [column][row]: rows k0 ..
     __shared__ double D[CHU][CHU + 1];   // [column][row]: the diagonal block
     __shared__ double cs[CHU][2];
+    __shared__ unsigned long long keep;  // rows of D that stay as they are in R
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t c0 = k0 + CHU + (int64_t)blockIdx.x * CHU;
     const int nc = (int)min<int64_t>(CHU, n - c0);
@@ -341,8 +342,10 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
         if (first) D[c][r] = dv[q];
     }
     __syncthreads();
-    // rows of P or D to R, by nthr threads: the LDS reads of a thread together
-    auto put = [&](const double (*M)[CHU + 1], int64_t r0, bool upper, int t, int nthr) {
+    // rows of P or D to R, by nthr threads (whole waves, so a thread's row is
+    // one): the LDS reads of a thread together
+    auto put = [&](const double (*M)[CHU + 1], int64_t r0, bool upper, int t, int nthr, unsigned long long not_rows) {
+        const bool skip = (not_rows >> (t & 63)) & 1;
         for (int i0 = t; i0 < CHU * CHU; i0 += 16 * nthr) {
             double x[16];
 #pragma unroll
@@ -355,7 +358,7 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
                 const int idx = i0 + nthr * q, r = idx & 63, c = idx >> 6;
-                if (c < nc && (!upper || r <= c)) HQR_AT(R, r0 + r, c0 + c, ldr) = x[q];
+                if (c < nc && (!upper || r <= c) && !skip) HQR_AT(R, r0 + r, c0 + c, ldr) = x[q];
             }
         }
     };
@@ -390,8 +393,8 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
         }
         __syncthreads();
         // in workgroup 0 the first wave goes on with the diagonal block
-        if (!first) put(P, k0, false, tid, 256);
-        else if (tid >= 64) put(P, k0, false, tid - 64, 192);
+        if (!first) put(P, k0, false, tid, 256, 0ull);
+        else if (tid >= 64) put(P, k0, false, tid - 64, 192, 0ull);
     }
     if (!first) return;
     // the previous block's rotations were used by the launch before this one,
@@ -438,15 +441,13 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
 #pragma unroll
             for (int i = 0; i < 16; ++i) D[lane][i0 + i] = a[i];
         }
-        const int64_t col = c0 + min(lane, nc - 1);
-        // a row whose rotation is none keeps its bits (a select in the steps
-        // lengthened their chain: 0.8 us a launch)
-        for (unsigned long long same = __ballot(lane < nc && cs[lane][1] == 0.0); same; same &= same - 1) {
-            const int k = __ffsll((long long)same) - 1;
-            D[lane][k] = HQR_AT(R, min(c0 + k, col), col, ldr);
-        }
+        // a row whose rotation is none keeps its bits: it is not stored (a
+        // select in the steps lengthened their chain by 0.8 us a launch)
+        unsigned long long same = __ballot(lane < nc && cs[lane][1] == 0.0);
         if (__ballot(lane < nc && !(my_d >= 0x1p-900 && my_d <= 0x1p900))) {
             vj = v0;
+            same = 0ull;
+            const int64_t col = c0 + min(lane, nc - 1);
             for (int k = 0; k < nc; ++k) {
                 const double x = HQR_AT(R, min(c0 + k, col), col, ldr);
                 double c, s, r;
@@ -458,9 +459,10 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
             }
         }
         if (lane < nc) v[c0 + lane] = last ? 0.0 : rot_pack(cs[lane][0], cs[lane][1]);
+        if (lane == 0) keep = same;
     }
     __syncthreads();
-    put(D, c0, true, tid, 256);
+    put(D, c0, true, tid, 256, keep);
 }
 
 } // namespace hqr
