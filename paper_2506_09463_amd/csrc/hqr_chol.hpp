@@ -465,4 +465,51 @@ __global__ void __launch_bounds__(256) chol_update_kernel(double *R, int64_t ldr
     put(D, c0, true, tid, 256, keep);
 }
 
+// The smallest updates, n <= CHU_SMALL: one wave, a column per lane, no steps
+// past the last row.  Bound: the launch, then n rotations (n = 8:
+// 9.9 us, 11.3 by the kernel above, whose group of 16 steps and 64 x 64 staging
+// are longer than the update).
+constexpr int CHU_SMALL = 15;
+
+__global__ void __launch_bounds__(64) chol_update_small_kernel(double *R, int64_t ldr, double *v, int n)
+{
+    __shared__ double D[CHU_SMALL][64];   // [row][column]
+    const int lane = threadIdx.x, col = min(lane, n - 1);
+    double a[CHU_SMALL];
+#pragma unroll
+    for (int i = 0; i < CHU_SMALL; ++i) a[i] = HQR_AT(R, min(i, col), col, ldr);
+    const double v0 = v[col];
+#pragma unroll
+    for (int i = 0; i < CHU_SMALL; ++i) D[i][lane] = a[i];
+    double vj = v0, my_d = 1.0, my_s = 1.0;   // lane k: of rotation k
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) {
+        const double x = D[k][lane], ak = readlane_f64(x, k), bk = readlane_f64(vj, k), d = fma(ak, ak, bk * bk);
+        double c, s, r;
+        rot_fast(ak, bk, d, c, s, r);
+        D[k][lane] = (lane == k) ? r : fma(c, x, s * vj);
+        vj = fma(c, vj, -(s * x));
+        my_d = (lane == k) ? d : my_d;
+        my_s = (lane == k) ? s : my_s;
+    }
+    // as above: rows whose rotation is none stay, a d out of range does all again
+    unsigned long long same = __ballot(lane < n && my_s == 0.0);
+    if (__ballot(lane < n && !(my_d >= 0x1p-900 && my_d <= 0x1p900))) {
+        vj = v0;
+        same = 0ull;
+#pragma unroll 1
+        for (int k = 0; k < n; ++k) {
+            const double x = HQR_AT(R, min(k, col), col, ldr);
+            double c, s, r;
+            rot_safe(readlane_f64(x, k), readlane_f64(vj, k), c, s, r);
+            D[k][lane] = (lane == k) ? r : fma(c, x, s * vj);
+            vj = (lane > k) ? fma(c, vj, -(s * x)) : vj;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < CHU_SMALL; ++i)
+        if (i <= lane && lane < n && !((same >> i) & 1)) HQR_AT(R, i, lane, ldr) = D[i][lane];
+    if (lane < n) v[lane] = 0.0;
+}
+
 } // namespace hqr

@@ -25,6 +25,10 @@ hipError_t k_chol_block(hipStream_t s, double *S, int64_t lds, int64_t n, int64_
 
 hipError_t k_chol_update(hipStream_t s, double *R, int64_t ldr, double *v, int64_t n)
 {
+    if (n <= CHU_SMALL) {
+        HQR_LAUNCH(K_REFINE, chol_update_small_kernel, dim3(1), dim3(64), 0, s, R, ldr, v, (int)n);
+        return hipGetLastError();
+    }
     for (int64_t k0 = -CHU; k0 + CHU < n; k0 += CHU) {
         const unsigned T = (k0 < 0) ? 1u : (unsigned)((n - k0 - CHU + CHU - 1) / CHU);
         HQR_LAUNCH(K_REFINE, chol_update_kernel, dim3(T), dim3(256), 0, s, R, ldr, v, n, k0);
