@@ -779,29 +779,33 @@ static StreamCtx *stream_ctx(hipStream_t caller)
     return &c;
 }
 
-// Work put on a context's side stream between fork() and join().  The
-// destructor joins too: when a call returns early (a launch failed), the
-// caller's stream still waits for what runs on the side stream, which may
-// read the workspace that is freed next in the caller's stream order.
+// Work put on a context's side stream between start() and join(): it begins
+// after what the caller's stream held at mark().  The destructor joins too:
+// when a call returns early (a launch failed), the caller's stream still waits
+// for what runs on the side stream, which may read the workspace that is
+// freed next in the caller's stream order.
 struct SideFork {
     StreamCtx *ctx = nullptr;
     hipStream_t s = nullptr;
-    hipError_t fork(StreamCtx *c, hipStream_t caller)
+    bool started = false;
+    hipError_t mark(StreamCtx *c, hipStream_t caller)
     {
-        hipError_t e = hipEventRecord(c->ev[3], caller);
-        if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->ev[3], 0);
-        if (e == hipSuccess) {
-            ctx = c;
-            s = caller;
-        }
+        ctx = c;
+        s = caller;
+        return hipEventRecord(c->ev[3], caller);
+    }
+    hipError_t start()
+    {
+        const hipError_t e = hipStreamWaitEvent(ctx->side, ctx->ev[3], 0);
+        started = e == hipSuccess;
         return e;
     }
     hipError_t join()
     {
-        if (!ctx) return hipSuccess;
+        if (!started) return hipSuccess;
         hipError_t e = hipEventRecord(ctx->ev[2], ctx->side);
         if (e == hipSuccess) e = hipStreamWaitEvent(s, ctx->ev[2], 0);
-        ctx = nullptr;
+        started = false;
         return e;
     }
     ~SideFork() { (void)join(); }
@@ -864,7 +868,8 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
     hipEvent_t ev_a = ss->ev[0], ev_r = ss->ev[1];
     // side stream starts after everything already on the caller's stream
     SideFork fork;
-    HQR_CK(fork.fork(ss, s));
+    HQR_CK(fork.mark(ss, s));
+    HQR_CK(fork.start());
     bool pending_r = false;
     if (have_t) {
         // Fused chain on the caller's stream, per panel p:
@@ -1429,39 +1434,60 @@ static int lsq_batched_impl(int count, const int64_t *m, const int64_t *n, const
     if (rc) return rc;
     HQR_CK(k_fill_int(stream, head, 0, (int64_t)4));
     HQR_CK(hipGetLastError());
-    // the one-workgroup groups side by side: the others fill the CUs that the
-    // longest factorizations leave (in one stream they would wait for the
-    // last of them)
-    hipStream_t s_rest = stream;
-    SideFork fork;
-    if (nfac > 0 && nfac < nwg && lookahead_enabled()) {
-        if (StreamCtx *ctx = stream_ctx(stream)) {
-            HQR_CK(fork.fork(ctx, stream));
-            s_rest = ctx->side;
+    // The one-workgroup groups side by side: the others fill the CUs that the
+    // longest one leaves (in one stream they would wait for its last
+    // instance).  The group that takes longest goes to the caller's stream,
+    // ahead of the side stream's launches, so that neither the fork nor the
+    // join stands on its path (one 300 x 20 beside one 128 x 64: 156 us with
+    // the 300 rows there, 129 so).  Below 10 us there is nothing to hide the
+    // fork behind (one stored 300 x 8 beside one 20 x 8: 64 us, 57 in one
+    // stream; 300 x 20 beside 20 x 8: 78 and 92).  Times in us from single
+    // instances on MI355X, within a third: 1.1 n + flops / 60000 to factor,
+    // n stored.
+    auto duration = [&](int lo, int hi) {
+        double longest = 0.0, sum = 0.0;
+        for (int i = lo; i < hi; ++i) {
+            const double mm = (double)sorted[i].m, nn = (double)sorted[i].n;
+            const double t = sorted[i].factor ? 1.1 * nn + (2.0 * mm - 2.0 / 3.0 * nn) * nn * nn / 6e4 : nn;
+            longest = std::max(longest, t);
+            sum += t;
         }
-    }
+        return std::max(longest, sum / num_cus());
+    };
+    struct Group {
+        int kind, lo, hi;   // kind as in fits; its queue head's index
+        double t;
+    } grp[3] = {{3, 0, nfac, 0.0}, {2, nfac, nrow, 0.0}, {1, nrow, nwg, 0.0}};
+    for (Group &q : grp) q.t = (q.hi > q.lo) ? duration(q.lo, q.hi) : -1.0;
+    std::stable_sort(grp, grp + 3, [](const Group &x, const Group &y) { return x.t > y.t; });
     const WgDesc *wd = (const WgDesc *)dbase;
-    if (nfac > 0) HQR_CK(k_wg_batched_rows(true, std::min(nfac, num_cus()), stream, wd, nfac, head + 2, info));
-    if (nrow > nfac)
-        HQR_CK(k_wg_batched_rows(false, std::min(nrow - nfac, num_cus()), s_rest, wd + nfac, nrow - nfac, head + 3,
-                                 info));
-    if (nwg > nrow) {
+    auto launch = [&](const Group &q, hipStream_t s) -> hipError_t {
+        const int k = q.hi - q.lo;
+        if (k <= 0) return hipSuccess;
+        if (q.kind > 1)
+            return k_wg_batched_rows(q.kind == 3, std::min(k, num_cus()), s, wd + q.lo, k, head + q.kind, info);
         int occ = tune_lookup(HQR_TUNE_OCCUPANCY, mmax, nmax, HQR_PREC_FP64);
         occ = (occ >= 1) ? std::min(occ, var->per_cu) : std::min(var->per_cu, 2);
-        const int grid = std::min(nwg - nrow, occ * num_cus());
-        HQR_CK(k_wg_batched(var, grid, s_rest, wd + nrow, nwg - nrow, head, info));
-    }
-    HQR_CK(fork.join());
+        return k_wg_batched(var, std::min(k, occ * num_cus()), s, wd + q.lo, k, head + q.kind, info);
+    };
+    StreamCtx *ctx = (grp[1].hi > grp[1].lo && grp[0].t >= 10.0 && lookahead_enabled()) ? stream_ctx(stream) : nullptr;
+    SideFork fork;
+    if (ctx) HQR_CK(fork.mark(ctx, stream));
+    HQR_CK(launch(grp[0], stream));
+    if (ctx) HQR_CK(fork.start());
+    HQR_CK(launch(grp[1], ctx ? ctx->side : stream));
+    HQR_CK(launch(grp[2], ctx ? ctx->side : stream));
     if (nwg < count) {
         BatchArgs a;
         a.desc = (const BatchDesc *)(dbase + sizeof(WgDesc) * (size_t)nwg);
         a.count = count - nwg;
-        a.head = head + 1;
+        a.head = head;
         a.info = info;
         a.max_ntot = max_ntot;
         const int grid = std::min(count - nwg, 2 * num_cus());
         HQR_CK(k_batched_lsq(dim3(grid), stream, a));
     }
+    HQR_CK(fork.join());
     return 0;
 }
 

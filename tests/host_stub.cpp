@@ -88,7 +88,9 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t, h
         const char *d = *(const char **)args[0];
         l += " rows=";
         for (int i = 0; i < *(const int *)args[1]; ++i) l += (i ? "," : "") + std::to_string(*(const int64_t *)(d + 88 * i));
+        l += " head=" + std::to_string(*(const uintptr_t *)args[2]);
     }
+    if (k.find("batched_lsq") != std::string::npos) l += " head=" + std::to_string(((const uintptr_t *)args[0])[2]);
     say(l);
     return hipSuccess;
 }

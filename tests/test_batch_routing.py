@@ -73,3 +73,52 @@ def test_bits_do_not_depend_on_the_batch_or_rules():
     finally:
         hqr.tune_clear()
         hqr.load_tune_db()
+
+
+ALL = [(400, 200, 2), (300, 20, 1), (100, 20, 1), (2000, 10, 1), (20, 8, 2), (1024, 16, 1)]
+
+
+def test_every_group_has_a_queue_of_its_own(host):
+    """New and stored instances above 256 rows, smaller ones and streamed ones
+    in one call: four launches, four queue heads, every instance in one."""
+    host.log()
+    assert host.batched(ALL, [0, 1, 0, 0, 1, 1]) == 0
+    log = [l for l in host.log() if "head=" in l]
+    assert len(log) == 4 and len({l.split("head=")[1] for l in log}) == 4
+    assert sum(l.startswith("launch batched_lsq_kernel") for l in log) == 1
+    rows = sorted(int(r) for l in log if "rows=" in l for r in l.split("rows=")[1].split()[0].split(","))
+    assert rows == sorted(m for m, _, _ in ALL if m <= 1024)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lookahead", ["1", "0"])
+@pytest.mark.parametrize("copies", [1, 60])
+def test_all_groups_in_one_batch(oracle_mod, monkeypatch, lookahead, copies):
+    import torch
+    import paper_2506_09463_amd as hqr
+    from tests.gpu_util import factor_tol, lsq_forward_bound, to_dev, to_host
+    monkeypatch.setenv("HQR_LOOKAHEAD", lookahead)
+    rng = np.random.default_rng(1450)
+    shapes = [(400, 200, 2), (300, 20, 1), (100, 20, 1), (2000, 10, 1), (20, 8, 2), (1024, 16, 1), (1500, 12, 1)] * copies
+    stored = [0, 1, 0, 0, 1, 1, 1] * copies
+    probs = [(rng.standard_normal((m, n)), rng.standard_normal((m, r))) for m, n, r in shapes]
+    print("[case] all groups", copies, lookahead, flush=True)
+    As = [to_dev(A) for A, _ in probs]
+    ups, _, _ = hqr.qr_lsq_solve_batched(As, [to_dev(B) for _, B in probs])
+    torch.cuda.synchronize()
+    for a, (A, _), s in zip(As, probs, stored):
+        if not s:
+            a.copy_(to_dev(A))
+    Bs = [to_dev(B) for _, B in probs]
+    info = torch.full((len(probs),), -5, dtype=torch.int32, device="cuda")
+    hqr.qr_lsq_solve_batched(As, Bs, ups=ups, info=info, factored=stored)
+    torch.cuda.synchronize()
+    assert not to_host(info).any()
+    for (A, B), a, b in zip(probs, As, Bs):
+        n = A.shape[1]
+        Xo, Fo = oracle_mod.lsq_solve(A, B)[:2]
+        assert np.abs(to_host(a) - Fo).max() <= factor_tol(A)
+        for c in range(B.shape[1]):
+            r = B[:, c] - A @ Xo[:, c]
+            x = to_host(b)[:n, c]
+            assert np.linalg.norm(x - Xo[:, c]) <= 2 * lsq_forward_bound(A, Xo[:, c], r) * np.linalg.norm(Xo[:, c])
