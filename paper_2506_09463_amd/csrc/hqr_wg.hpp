@@ -572,7 +572,9 @@ HQR_DEV void wg_panel_factor(const WgDesc &d, int c0, int pw, WgShared<NT, QM> &
             }
         }
     };
-    if (pw == WG_P) store(true);
+    // (with 512 threads the second copy costs more than it gives: 2000
+    // instances 15.40 ms with it, 15.34 without)
+    if (!WgShared<NT, QM>::ROWS && pw == WG_P) store(true);
     else store(false);
     __syncthreads();
     wg_panel_t<NT, QM>(nrows, pw, sh);
