@@ -54,15 +54,16 @@ HBM_TRAFFIC = {
 C2_KERNEL_SOURCES = ("hqr_args.hpp", "hqr_device.hpp", "hqr_blocked.hpp", "hqr_chol64.hpp", "hqr_cqr.hpp", "k_blocked.hip",
                      "k_cqr.hip")
 
-# HBM bytes of the batched workload's one launch (read, write), from the same
-# two counters and scaling; valid for the one-workgroup kernel's sources, the
-# tuning database (which picks the variant) and the batch recipe hashed here.
+# HBM bytes of the batched workload's launches (read, write), from the same
+# two counters and scaling; valid for the one-workgroup kernels' sources, the
+# host dispatch (which picks each instance's kernel), the tuning database (the
+# variant up to 256 rows) and the batch recipe hashed here.
 BATCHED_TRAFFIC = {
     "sha256": "28e71dc2dff17136784fa7f16f4cd614d23f174b3782add429ad80007ba199ad",
     "bytes": [41010364032, 22412739968],
 }
-BATCHED_SOURCES = ("csrc/hqr_args.hpp", "csrc/hqr_device.hpp", "csrc/hqr_wg.hpp", "csrc/k_wg.hip", "tune_db.json",
-                   "workloads.py")
+BATCHED_SOURCES = ("csrc/hqr_args.hpp", "csrc/hqr_device.hpp", "csrc/hqr_wg.hpp", "csrc/k_wg.hip", "csrc/hqr_lib.hip",
+                   "tune_db.json", "workloads.py")
 
 
 def csrc_sha256(names=None, prefix="csrc"):
@@ -431,7 +432,7 @@ def _line(metric_unit, value, ms, args, config, roofline=None, cpu=None, hib=Tru
 
 
 def run_batched(args):
-    """2000 uneven instances (n ~ U{16..512}, m = n + U{0..n}, 8 RHS) in one launch."""
+    """2000 uneven instances (n ~ U{16..512}, m = n + U{0..n}, 8 RHS) in one call."""
     import torch
     import paper_2506_09463_amd as hqr
     from paper_2506_09463_amd import workloads
@@ -458,7 +459,7 @@ def run_batched(args):
             b.copy_(b0)
 
     # the pointer arrays are marshalled once (the buffers are reused); a step
-    # is the library call: LPT order, descriptors, upload, persistent launch
+    # is the library call: LPT order, descriptors, upload, persistent launches
     plan = hqr.BatchPlan(As, Bs, ups=ups, resnorms=res, info=info, work=work)
     for _ in range(args.warmup):
         restore()
@@ -512,7 +513,7 @@ def run_batched(args):
         dt = time.perf_counter() - t0
         cpu = {"value": k / dt, "unit": "solves/s", "cores": 1, "kind": "oracle",
                "sample": "oracle lsq_solve of the first %d instances of the batch (caller order), %.1f s" % (k, dt)}
-    cfg = {"workload": "batched FP64 LSQ: %d instances, n ~ U{16..512}, m = n + U{0..n}, 8 RHS, one persistent launch"
+    cfg = {"workload": "batched FP64 LSQ: %d instances, n ~ U{16..512}, m = n + U{0..n}, 8 RHS, one call"
            % len(probs), "count": len(probs), "factor_gflop": fl / 1e9, "total_gflop": fl_all / 1e9,
            "loop_of_single_solves_ms": loop_ms, "speedup_vs_loop": loop_ms / ms}
     print(json.dumps(_line(("batched LSQ solves/s", "solves/s"), len(probs) / (ms * 1e-3), ms, args, cfg, roof, cpu)),

@@ -262,9 +262,9 @@ int qr_lsq_refine(int64_t m, int64_t n, int64_t nrhs, const double *A,
                   int64_t lda_orig, void *work, int64_t lwork, int *info,
                   int *iters, hipStream_t stream);
 
-/* Many independent least-squares problems of uneven size in ONE persistent
- * launch (a batch of the per-iteration subproblems an SLSQP-like solver
- * produces).  Arrays of length `count` are HOST arrays; A[i], up[i], B[i],
+/* Many independent least-squares problems of uneven size in one call (a batch
+ * of the per-iteration subproblems an SLSQP-like solver produces): at most
+ * four persistent launches, by the instances' own shapes, side by side.  Arrays of length `count` are HOST arrays; A[i], up[i], B[i],
  * resnorm[i] are device pointers.  Instance i: m[i] x n[i] (n[i] <= m[i] <=
  * 4096), nrhs[i] right-hand sides (n[i] + nrhs[i] <= 2048); A[i] is factored
  * in place exactly as by qr_factor's one-reflector-at-a-time definition,
@@ -282,8 +282,7 @@ int qr_lsq_solve_batched(int count, const int64_t *m, const int64_t *n,
                          double *const *resnorm, int *info, void *work,
                          int64_t lwork, hipStream_t stream);
 
-/* The same persistent launch over a mix of new and already-factored
- * problems (factor reuse across successive solves): factored[i] (HOST int
+/* The same call over a mix of new and already-factored problems (factor reuse across successive solves): factored[i] (HOST int
  * array) nonzero means A[i] and up[i] already hold qr_factor's output for
  * instance i, which is then only applied to B[i] (Q^T B, residual norms,
  * back-substitution; A[i], up[i] untouched); zero means factor as in

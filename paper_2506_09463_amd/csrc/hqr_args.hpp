@@ -121,7 +121,7 @@ struct WArgs {
 constexpr int WS_COLS = 16;
 
 // Narrow form (at most 64 columns, many row splits): 4 columns per
-// workgroup, thread (row i, column c) sums its partials 16 at a time.
+// workgroup, thread (row i, column c) sums its partials 32 at a time.
 constexpr int WSN_COLS = 4;
 
 // ---------------------------------------------------------- X <- X - V W'
@@ -150,7 +150,7 @@ struct UpdArgs {
 // four 128-byte segments.
 constexpr int UPD_TILE = 128;
 
-// Blocked back-substitution R X = B[0:n].  Row blocks of 64; workgroup b
+// Blocked back-substitution R X = B[0:n].  Row blocks of TRSV_ROWS; workgroup b
 // owns row block nblk-1-b, so every block it waits for belongs to a
 // workgroup dispatched before it.  A block is published by storing its x
 // values into xpub, whose slots hold the TRSV_EMPTY pattern until then: each

@@ -1,5 +1,6 @@
 // hqr_batched.hpp -- many independent least-squares problems of uneven size
-// in one persistent launch.
+// in one persistent launch: those a workgroup's registers and LDS do not hold
+// (the others go to hqr_wg.hpp).
 //
 // Each workgroup (1024 threads) repeatedly takes the next instance from an
 // atomic queue head (instances sorted longest-first on the host, so the

@@ -165,17 +165,6 @@ __global__ void __launch_bounds__(256) panel_col_kernel(PanelArgs p)
 }
 
 
-// V element (global row gi >= c0, panel column c) with both candidate loads
-// issued unconditionally (no branch around a load, so a tile's loads stay in
-// flight together); gi and c must address the matrix.
-HQR_DEV double v_elem_nb(const double *A, int64_t lda, const double *up, int c0, int64_t gi, int c)
-{
-    const double a = HQR_AT(A, gi, c0 + c, lda);
-    const double u = up[c0 + c];
-    const int64_t d = gi - c0;
-    return (d < c) ? 0.0 : ((d == c) ? u : a);
-}
-
 // F32: operands rounded to FP32, FP32 MFMA with FP32 accumulation (the
 // partial sums are stored widened to FP64).  WITHV: the first bw X columns
 // are the panel's own V columns (the per-column panel mode forms V^T V there).

@@ -221,7 +221,6 @@ struct Plan {
     int nblk;        // triangular blocks
     int ngroups;     // CholeskyQR row groups of the first panel (upper bound)
     int npanels;
-    int nb;          // panel width (<= NB)
     bool f32;        // trailing-update contractions in FP32
     bool no_side;    // no look-ahead side stream (one stream only)
     bool tsqr;       // TSQR panels (workspace for the tree included)
@@ -229,10 +228,9 @@ struct Plan {
 
 static int64_t rup(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
-static Plan make_plan(int64_t m, int64_t n, int64_t nrhs, int nb = NB, bool f32 = false)
+static Plan make_plan(int64_t m, int64_t n, int64_t nrhs, bool f32 = false)
 {
     Plan p;
-    p.nb = nb;
     p.f32 = f32;
     p.m = m;
     p.n = n;
@@ -242,7 +240,7 @@ static Plan make_plan(int64_t m, int64_t n, int64_t nrhs, int nb = NB, bool f32 
     p.nsplit_max = 16;
     p.nblk = (int)((n + TRSV_ROWS - 1) / TRSV_ROWS);
     p.ngroups = (int)((m + CQR_ROWS - 1) / CQR_ROWS);
-    p.npanels = (int)((n + nb - 1) / nb);
+    p.npanels = (int)((n + NB - 1) / NB);
     p.no_side = false;
     p.tsqr = panel_mode() == PANEL_TSQR;
     return p;
@@ -850,9 +848,9 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
         return panel_cqr(pl, w, A, lda, up, (int)c0, bw, pidx, Tbuf[pidx & 1], s);
     };
     if (!ss) {
-        for (int64_t c0 = 0; c0 < n; c0 += pl.nb) {
-            const int bw = (int)std::min<int64_t>(pl.nb, n - c0);
-            const int pidx = (int)(c0 / pl.nb);
+        for (int64_t c0 = 0; c0 < n; c0 += NB) {
+            const int bw = (int)std::min<int64_t>(NB, n - c0);
+            const int pidx = (int)(c0 / NB);
             int rc = do_panel(c0, bw, pidx);
             if (rc) return rc;
             const int ncA = (int)(n - c0 - bw);
@@ -882,14 +880,14 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
         // MFMA rate), the later columns and B FP32 in R(p).  It took the
         // mixed 3000 x 2048 solve from 6.80 to 5.88 ms against a chain of
         // separate V_bot, V^T C, T, W' and FP32 update launches.
-        const int bw0 = (int)std::min<int64_t>(pl.nb, n);
+        const int bw0 = (int)std::min<int64_t>(NB, n);
         int rc = panel_passes(pl, w, A, lda, up, 0, bw0, 0, Tbuf[0], false, 0, s);
         if (rc) return rc;
-        for (int64_t c0 = 0; c0 < n; c0 += pl.nb) {
-            const int bw = (int)std::min<int64_t>(pl.nb, n - c0);
-            const int pidx = (int)(c0 / pl.nb);
+        for (int64_t c0 = 0; c0 < n; c0 += NB) {
+            const int bw = (int)std::min<int64_t>(NB, n - c0);
+            const int pidx = (int)(c0 / NB);
             const int64_t c1 = c0 + bw;
-            const int bw1 = (int)std::min<int64_t>(pl.nb, std::max<int64_t>(0, n - c1));
+            const int bw1 = (int)std::min<int64_t>(NB, std::max<int64_t>(0, n - c1));
             const int ncR = (int)std::max<int64_t>(0, n - c1 - bw1);
             TrailBufs br = bufR;
             br.T = Tbuf[pidx & 1];
@@ -905,7 +903,7 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
                 // late panels, where the main chain is the longer one: V^T C
                 // on at most half the CUs so the chain's kernels find free ones
                 rc = apply_panel_block(pl, br, A, lda, B, ldb, up, (int)c0, bw, bw1, ncR, nB, true, ss->side, pl.f32,
-                                       std::min(ncR, (int)pl.nb), ev_r, (ncR + nB <= 2048) ? 128 : 0);
+                                       std::min(ncR, NB), ev_r, (ncR + nB <= 2048) ? 128 : 0);
                 if (rc) return rc;
             } else {
                 HQR_CK(hipEventRecord(ev_r, ss->side));
@@ -927,13 +925,13 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
         HQR_CK(fork.join());
         return 0;
     }
-    int rc = do_panel(0, (int)std::min<int64_t>(pl.nb, n), 0);
+    int rc = do_panel(0, (int)std::min<int64_t>(NB, n), 0);
     if (rc) return rc;
-    for (int64_t c0 = 0; c0 < n; c0 += pl.nb) {
-        const int bw = (int)std::min<int64_t>(pl.nb, n - c0);
-        const int pidx = (int)(c0 / pl.nb);
+    for (int64_t c0 = 0; c0 < n; c0 += NB) {
+        const int bw = (int)std::min<int64_t>(NB, n - c0);
+        const int pidx = (int)(c0 / NB);
         const int64_t c1 = c0 + bw;                       // next panel
-        const int bw1 = (int)std::min<int64_t>(pl.nb, std::max<int64_t>(0, n - c1));
+        const int bw1 = (int)std::min<int64_t>(NB, std::max<int64_t>(0, n - c1));
         const int ncR = (int)std::max<int64_t>(0, n - c1 - bw1);
         TrailBufs bn = bufN, br = bufR;
         bn.T = br.T = Tbuf[pidx & 1];
@@ -946,7 +944,7 @@ static int factor_blocked(const Plan &pl, const Work &w, double *A, int64_t lda,
         HQR_CK(hipStreamWaitEvent(ss->side, ev_a, 0));
         if (ncR + nB > 0) {
             rc = apply_panel_block(pl, br, A, lda, B, ldb, up, (int)c0, bw, bw1, ncR, nB, have_t, ss->side, pl.f32,
-                                   std::min(ncR, (int)pl.nb), ev_r);
+                                   std::min(ncR, NB), ev_r);
             if (rc) return rc;
         } else {
             HQR_CK(hipEventRecord(ev_r, ss->side));
@@ -1256,7 +1254,7 @@ static int lsq_mixed(int64_t m, int64_t n, int64_t nrhs, double *A, int64_t lda,
     const double tol = (opt && opt->tol > 0.0) ? opt->tol : 1e-13;
     const int max_iter = (opt && opt->max_iter >= 0) ? opt->max_iter : 10;
     const bool async = no_fallback(opt);
-    Plan pl = make_plan(m, n, nrhs, NB, true);
+    Plan pl = make_plan(m, n, nrhs, true);
     pl.tsqr = pl.tsqr || tsqr_opt(opt);
     WorkGuard g;
     Work w;
@@ -1516,7 +1514,7 @@ int64_t hqr_workspace_size(int64_t m, int64_t n, int64_t nrhs, int precision)
     if (n < 0 || n > m) return -2;
     if (nrhs < 0) return -3;
     if (precision != HQR_PREC_FP64 && precision != HQR_PREC_MIXED) return -4;
-    Plan pl = (precision == HQR_PREC_MIXED) ? make_plan(m, n, nrhs, NB, true) : make_plan(m, n, nrhs);
+    Plan pl = (precision == HQR_PREC_MIXED) ? make_plan(m, n, nrhs, true) : make_plan(m, n, nrhs);
     return (int64_t)work_bytes(pl, nullptr, nullptr);
 }
 
@@ -1525,7 +1523,7 @@ int64_t hqr_workspace_size_opts(int64_t m, int64_t n, int64_t nrhs, const hqr_op
     const int precision = opt ? opt->precision : HQR_PREC_FP64;
     const int64_t base = hqr_workspace_size(m, n, nrhs, precision);
     if (base < 0 || !tsqr_opt(opt)) return base;
-    Plan pl = (precision == HQR_PREC_MIXED) ? make_plan(m, n, nrhs, NB, true) : make_plan(m, n, nrhs);
+    Plan pl = (precision == HQR_PREC_MIXED) ? make_plan(m, n, nrhs, true) : make_plan(m, n, nrhs);
     pl.tsqr = true;
     return (int64_t)work_bytes(pl, nullptr, nullptr);
 }
@@ -1925,7 +1923,7 @@ int qr_lsq_refine(int64_t m, int64_t n, int64_t nrhs, const double *A, int64_t l
     const double tol = (opt && opt->tol > 0.0) ? opt->tol : 1e-13;
     const int max_iter = (opt && opt->max_iter >= 0) ? opt->max_iter : 10;
     const bool async = no_fallback(opt);
-    Plan pl = make_plan(m, n, nrhs, NB, true);
+    Plan pl = make_plan(m, n, nrhs, true);
     WorkGuard g;
     Work w;
     int rc = get_work(pl, work, lwork, stream, g, &w);

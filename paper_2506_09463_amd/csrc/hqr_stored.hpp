@@ -80,8 +80,8 @@ __global__ void __launch_bounds__(256) stored_gram_kernel(StoredGramArgs p)
 // So a panel costs one launch (rows of V are read twice, B once), where V^T B,
 // T, W' and the update were four.  Every workgroup sums the same parts in the
 // same order.  Bound: latency (launch, one round of loads, three 64-deep
-// MFMA products, the stores).  2047 x 1500, three columns, on MI355X: 11.3 us a
-// panel, Q^T b and the solve 0.45 ms; four launches of 7 to 20 us and 1.31 ms
+// MFMA products, the stores).  2047 x 1500, three columns, on MI355X: 11.0 us a
+// panel, Q^T b and the solve 0.376 ms; four launches of 7 to 20 us and 1.31 ms
 // before.
 __global__ void __launch_bounds__(256) stored_step_kernel(StoredStepArgs p)
 {

@@ -508,7 +508,7 @@ class BatchPlan:
 
 
 def qr_lsq_solve_batched(As, Bs, ups=None, resnorms=None, info=None, work=None, stream=None, factored=None):
-    """Solve a list of least-squares problems in one persistent launch.
+    """Solve a list of least-squares problems in one call.
 
     As, Bs: lists of column-major float64 device tensors (A_i m_i x n_i,
     B_i m_i x nrhs_i), overwritten in place like qr_lsq_solve.  Returns

@@ -21,7 +21,7 @@ Scheduling policy (host side; the GPU work is libhqr's):
     launch classes (``launch_class(r) -> (key, group limit)``): the class of
     the oldest ready request is launched next, as one group of at most its
     limit in arrival order.  The GPU executor's classes are "batched" (all
-    small requests in one persistent launch) and "single" (one large request
+    small requests in one batched call) and "single" (one large request
     per launch), so a small request never waits for a large one launched
     beside it, and large ones complete one by one; without classes all
     ready requests go into one batch;
@@ -322,7 +322,7 @@ class Server:
 class GpuExecutor:
     """Runs batches through libhqr on `nstreams` torch streams.
 
-    Instances with n <= ``batch_n_max`` go to one persistent batched launch
+    Instances with n <= ``batch_n_max`` go to one batched call
     per batch (FP64); larger ones are solved one by one with the whole-GPU
     path on the same stream, after the batched launch: FP64 requests by
     qr_lsq_solve (cached factors: qr_apply_qt + qr_backsolve), mixed ones by
