@@ -42,12 +42,12 @@ PEAK_HBM_GBS = 8000.0
 # launches (update: the 64-column launch for panel p+2 and the bulk launch;
 # gram_reduce: the two Gram reductions and the X/W reduction).
 HBM_TRAFFIC = {
-    "csrc_sha256": "f54c4f5036ab3d3bfd8fc23efb83dd58192a88f2b74df80f766175199e9fccc4",
-    "per_launch_bytes": {"update": [73637700, 55161771], "vtx": [130921559, 15503360],
-                         "wsolve": [15226391, 1001984], "trsv": [68917337, 65536],
-                         "cqr_gram1": [6731192, 6294032], "cqr_gram2": [3524511, 3194880],
-                         "cqr_chol": [198140, 82176], "cqr_finish": [2447281, 2097152],
-                         "narrow_vtx": [6770741, 6324224], "gram_reduce": [3307072, 32779]},
+    "csrc_sha256": "3c0466e8ab58f2f2dba7e406730b74e10b111c7cfefdd495a9bae8e3760c3c66",
+    "per_launch_bytes": {"update": [73636045, 55163700], "vtx": [130926384, 15503360],
+                         "wsolve": [15216294, 1001984], "trsv": [68788992, 65536],
+                         "cqr_gram1": [6779152, 6294032], "cqr_gram2": [3541072, 3194880],
+                         "cqr_chol": [192450, 82176], "cqr_finish": [2468864, 2097152],
+                         "narrow_vtx": [6796591, 6324224], "gram_reduce": [3306479, 32779]},
 }
 
 
@@ -59,8 +59,8 @@ C2_KERNEL_SOURCES = ("hqr_args.hpp", "hqr_device.hpp", "hqr_blocked.hpp", "hqr_c
 # host dispatch (which picks each instance's kernel), the tuning database (the
 # variant up to 256 rows) and the batch recipe hashed here.
 BATCHED_TRAFFIC = {
-    "sha256": "28e71dc2dff17136784fa7f16f4cd614d23f174b3782add429ad80007ba199ad",
-    "bytes": [41010364032, 22412739968],
+    "sha256": "c50c3983b87ff734af2ae177e54877c9693516b60091aee39f2ecdb94986f5e9",
+    "bytes": [23925440768, 22781371520],
 }
 BATCHED_SOURCES = ("csrc/hqr_args.hpp", "csrc/hqr_device.hpp", "csrc/hqr_wg.hpp", "csrc/k_wg.hip", "csrc/hqr_lib.hip",
                    "tune_db.json", "workloads.py")
