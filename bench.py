@@ -42,7 +42,7 @@ PEAK_HBM_GBS = 8000.0
 # launches (update: the 64-column launch for panel p+2 and the bulk launch;
 # gram_reduce: the two Gram reductions and the X/W reduction).
 HBM_TRAFFIC = {
-    "csrc_sha256": "3c0466e8ab58f2f2dba7e406730b74e10b111c7cfefdd495a9bae8e3760c3c66",
+    "csrc_sha256": "fb76bdc5cb342133f33b6170c804918755ad507674bb8b6e4b807f713e4a0d25",
     "per_launch_bytes": {"update": [73636045, 55163700], "vtx": [130926384, 15503360],
                          "wsolve": [15216294, 1001984], "trsv": [68788992, 65536],
                          "cqr_gram1": [6779152, 6294032], "cqr_gram2": [3541072, 3194880],
@@ -59,7 +59,7 @@ C2_KERNEL_SOURCES = ("hqr_args.hpp", "hqr_device.hpp", "hqr_blocked.hpp", "hqr_c
 # host dispatch (which picks each instance's kernel), the tuning database (the
 # variant up to 256 rows) and the batch recipe hashed here.
 BATCHED_TRAFFIC = {
-    "sha256": "c50c3983b87ff734af2ae177e54877c9693516b60091aee39f2ecdb94986f5e9",
+    "sha256": "d7eb2c42cd09318639b3cf794f388ecc5a0d168061cd4c3d7068d114386ab2dd",
     "bytes": [23925440768, 22781371520],
 }
 BATCHED_SOURCES = ("csrc/hqr_args.hpp", "csrc/hqr_device.hpp", "csrc/hqr_wg.hpp", "csrc/k_wg.hip", "csrc/hqr_lib.hip",

@@ -317,7 +317,9 @@ struct NarrowArgs {
 // the quarters added 0..3), then column j of W = T^T X (T upper triangular,
 // W[i][j] = sum_{l <= i} T[l][i] X[l][j]; thread (i, g4) takes l in
 // [16 g4, 16 g4 + 16), the quarters added 0..3), stored transposed
-// (Wt[j][i]).  Under 64 VGPRs, so it can start beside two bulk waves per SIMD.
+// (Wt[j][i]).  T's loads are in flight beside the partials': 80 VGPRs, 5.7 ->
+// 5.0 us where the chain alone binds (701 x 333), though it then cannot start
+// beside two bulk waves per SIMD (8192 x 4096: 8.9 -> 11.0 us on average).
 struct XwArgs {
     const double *gpart;      // [parts][NB][NB], [q][j][i]
     int parts;
